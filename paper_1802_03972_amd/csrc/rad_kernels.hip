@@ -247,74 +247,128 @@ __global__ void k_tracked_finalize(const double* __restrict__ T, const double* _
     I[(int64_t)d * n_omega + k] = C * (s0 * s0 + s1 * s1 + s2 * s2 + s3 * s3);
 }
 
-// S[p] += sum over splits of part[s][p] for every grid point p (four components: S1r,
-// S1i, S2r, S2i), in split order, in FP64.  One thread per point reads 16 B per split with
-// kFoldUnroll loads in flight (the partials are read once: non-temporal loads), so few
-// waves keep HBM busy while the next push's accumulate holds the rest of the CUs.
-constexpr int kFoldUnroll = 16;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// FP64 sum of the FP32 partials *at(k), k in [k0, k1), in order, with U 16-byte loads in
+// flight; in the last round what is past the end is the last one again and not added.
+template <int U, typename At>
+__device__ __forceinline__ void fold_range(int k0, int k1, At at, double (&a)[4])
+{
+    auto add = [&](const f32x4& v) {
+        a[0] += (double)v.x;
+        a[1] += (double)v.y;
+        a[2] += (double)v.z;
+        a[3] += (double)v.w;
+    };
+    f32x4 v[U];
+    int k = k0;
+    for (; k + U <= k1; k += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(at(k + u));
+#pragma unroll
+        for (int u = 0; u < U; ++u) add(v[u]);
+    }
+    if (k < k1) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(at(k + u < k1 ? k + u : k1 - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k + u < k1) add(v[u]);
+    }
+}
+
+// The G groups' sums of PT points, added in group order: thread t < 4 PT gets component
+// t % 4 of point t / 4.
+template <int G, int PT>
+__device__ __forceinline__ double fold_groups(double (&red)[G][4 * PT], int p, int q, const double (&a)[4])
+{
+    static_assert(4 * PT <= 256, "one component per thread");
+#pragma unroll
+    for (int c = 0; c < 4; ++c) red[q][4 * p + c] = a[c];
+    __syncthreads();
+    double s = 0.0;
+    const int t = threadIdx.x;
+    if (t < 4 * PT) {
+#pragma unroll
+        for (int r = 0; r < G; ++r) s += red[r][t];
+    }
+    return s;
+}
+
+// S[p] += sum over splits of part[s][p] for every grid point p (four components: S1r,
+// S1i, S2r, S2i) in FP64, in a fixed order.  Bound by the one read of the partials (16 B
+// per split and point, non-temporal), and on small grids by the latency of that read: a
+// block of 256 threads is PT = 256 / G points x G groups of consecutive splits, with
+// kFoldUnroll loads in flight per thread (twice that without groups), so that a grid of a
+// few hundred points is not one serial chain of loads.  The groups' sums are added in group
+// order through LDS.  157 splits x 3700 points (9.3 MB): 16.5 us with one thread per point,
+// 6.0 us with 16 groups; 63 splits x 482 points: 10.9 and 4.3 us; 128 splits x 32768 points
+// (67 MB): 12.7 us (5.3 TB/s) without groups.
+constexpr int kFoldUnroll = 8;
+
+template <int G>
 __global__ void __launch_bounds__(256) k_fold(const f32x4* __restrict__ part, double* __restrict__ S,
                                               int splits, int64_t points)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= points) return;
-    const f32x4* p = part + i;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int k = 0;
-    for (; k + kFoldUnroll <= splits; k += kFoldUnroll) {
-        f32x4 v[kFoldUnroll];
-#pragma unroll
-        for (int u = 0; u < kFoldUnroll; ++u) v[u] = __builtin_nontemporal_load(p + (int64_t)(k + u) * points);
-#pragma unroll
-        for (int u = 0; u < kFoldUnroll; ++u) {
-            a0 += (double)v[u].x;
-            a1 += (double)v[u].y;
-            a2 += (double)v[u].z;
-            a3 += (double)v[u].w;
+    constexpr int PT = 256 / G;
+    const int p = threadIdx.x % PT, q = threadIdx.x / PT;
+    const int64_t i0 = (int64_t)blockIdx.x * PT;
+    const int64_t i = i0 + p < points ? i0 + p : points - 1;
+    const int per = (splits + G - 1) / G;
+    const int k0 = q * per, k1 = k0 + per < splits ? k0 + per : splits;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    fold_range<G == 1 ? 2 * kFoldUnroll : kFoldUnroll>(k0, k1, [&](int k) { return part + (int64_t)k * points + i; }, a);
+    if constexpr (G == 1) {
+        if (i0 + p < points) {
+            double2* s2 = reinterpret_cast<double2*>(S) + 2 * i;
+            double2 lo = s2[0], hi = s2[1];
+            lo.x += a[0]; lo.y += a[1]; hi.x += a[2]; hi.y += a[3];
+            s2[0] = lo;
+            s2[1] = hi;
         }
+    } else {
+        __shared__ double red[G][4 * PT];
+        const double s = fold_groups<G, PT>(red, p, q, a);
+        const int t = threadIdx.x;
+        if (t < 4 * PT && 4 * i0 + t < 4 * points) S[4 * i0 + t] += s;
     }
-    for (; k < splits; ++k) {
-        const f32x4 v = __builtin_nontemporal_load(p + (int64_t)k * points);
-        a0 += (double)v.x;
-        a1 += (double)v.y;
-        a2 += (double)v.z;
-        a3 += (double)v.w;
-    }
-    double2* s2 = reinterpret_cast<double2*>(S) + 2 * i;
-    double2 lo = s2[0], hi = s2[1];
-    lo.x += a0;
-    lo.y += a1;
-    hi.x += a2;
-    hi.y += a3;
-    s2[0] = lo;
-    s2[1] = hi;
 }
 
 // Batched fold: for every (grid, tile) job and every in-grid point of the tile, add the
-// listed segments' partial values (in list order, FP64) into the grid's S.
-__global__ void k_fold_batch(const int32_t* __restrict__ n_jobs_dev, const FoldJob* __restrict__ jobs,
-                             const int32_t* __restrict__ seg_list, const float4* __restrict__ seg_part,
-                             int TD, int TO)
+// listed segments' partial values (in list order within a group, then in group order, FP64)
+// into the grid's S.  As k_fold: PT elements of a tile x G groups of the job's list; the
+// lists are as uneven as the bunches (1 to several hundred segments), so the groups also
+// shorten the longest one.  12 bunches, 64 x 256 points each, 1024 ranges (137 MB): 73 us
+// with one thread per element and one load in flight, 26.5 us (5.2 TB/s) here.
+constexpr int kBatchFoldGroups = 8;
+constexpr int kBatchFoldPoints = 256 / kBatchFoldGroups;
+
+__global__ void __launch_bounds__(256) k_fold_batch(const int32_t* __restrict__ n_jobs_dev,
+                                                    const FoldJob* __restrict__ jobs,
+                                                    const int32_t* __restrict__ seg_list,
+                                                    const f32x4* __restrict__ seg_part, int TD, int TO)
 {
+    constexpr int G = kBatchFoldGroups, PT = kBatchFoldPoints;
+    __shared__ double red[G][4 * PT];
     const int n_jobs = *n_jobs_dev;
-    const int64_t per_job = (int64_t)TD * TO;
-    const int64_t total = per_job * n_jobs;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int jb = (int)(idx / per_job);
-        const int e = (int)(idx % per_job);
-        const FoldJob fj = jobs[jb];
-        const int og = fj.tw * TO + e / TD;
-        const int dg = fj.td * TD + e % TD;
-        if (og >= fj.n_omega || dg >= fj.n_dir) continue;
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-        for (int k = fj.list_begin; k < fj.list_end; ++k) {
-            const float4 v = seg_part[(int64_t)seg_list[k] * per_job + e];
-            a0 += (double)v.x; a1 += (double)v.y; a2 += (double)v.z; a3 += (double)v.w;
-        }
-        double* S = fj.S + ((int64_t)og * fj.n_dir + dg) * 4;
-        S[0] += a0; S[1] += a1; S[2] += a2; S[3] += a3;
+    const int per_job = TD * TO;                  // a multiple of 64
+    const int blocks_per_job = per_job / PT;
+    const int64_t total = (int64_t)blocks_per_job * n_jobs;
+    const int p = threadIdx.x % PT, q = threadIdx.x / PT;
+    for (int64_t blk = blockIdx.x; blk < total; blk += gridDim.x) {
+        const FoldJob fj = jobs[blk / blocks_per_job];
+        const int e0 = (int)(blk % blocks_per_job) * PT;
+        const int n = fj.list_end - fj.list_begin;
+        const int per = (n + G - 1) / G;
+        const int k0 = fj.list_begin + q * per;
+        const int k1 = k0 + per < fj.list_end ? k0 + per : fj.list_end;
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+        fold_range<kFoldUnroll>(k0, k1, [&](int k) { return seg_part + (int64_t)seg_list[k] * per_job + e0 + p; }, a);
+        const double s = fold_groups<G, PT>(red, p, q, a);
+        const int t = threadIdx.x, e = e0 + t / 4;
+        const int og = fj.tw * TO + e / TD, dg = fj.td * TD + e % TD;
+        if (t < 4 * PT && og < fj.n_omega && dg < fj.n_dir) fj.S[((int64_t)og * fj.n_dir + dg) * 4 + t % 4] += s;
+        __syncthreads();
     }
 }
 
@@ -378,26 +432,45 @@ hipError_t launch_fold_batch(const int32_t* n_jobs_dev, const FoldJob* jobs, int
                              const int32_t* seg_list, const float* seg_part, int td, int to, hipStream_t st)
 {
     if (max_jobs <= 0) return hipSuccess;
-    const int64_t total = (int64_t)max_jobs * td * to;
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 4096);
+    const int64_t total = (int64_t)max_jobs * td * to / kBatchFoldPoints;
+    const int blocks = (int)std::min<int64_t>(total, 16384);
     hipLaunchKernelGGL(k_fold_batch, dim3(blocks), dim3(256), 0, st, n_jobs_dev, jobs, seg_list,
-                       reinterpret_cast<const float4*>(seg_part), td, to);
+                       reinterpret_cast<const f32x4*>(seg_part), td, to);
     return hipGetLastError();
 }
+
+namespace {
+
+template <int G>
+hipError_t launch_fold_g(const f32x4* part, double* S, int splits, int64_t points, hipStream_t st,
+                         hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    const dim3 grid(grid1d(points, 256 / G));
+    if (ev_start || ev_stop) {
+        void* args[] = {&part, &S, &splits, &points};
+        return hipExtLaunchKernel(reinterpret_cast<const void*>(k_fold<G>), grid, dim3(256), args, 0, st, ev_start,
+                                  ev_stop, 0);
+    }
+    hipLaunchKernelGGL(k_fold<G>, grid, dim3(256), 0, st, part, S, splits, points);
+    return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t launch_fold(const float* part, double* S, int splits, int64_t count, hipStream_t st,
                        hipEvent_t ev_start, hipEvent_t ev_stop)
 {
-    int64_t points = count / 4;
+    const int64_t points = count / 4;
     if (points <= 0) return hipSuccess;
     const f32x4* p4 = reinterpret_cast<const f32x4*>(part);
-    if (ev_start || ev_stop) {
-        void* args[] = {&p4, &S, &splits, &points};
-        return hipExtLaunchKernel(reinterpret_cast<const void*>(k_fold), dim3(grid1d(points, 256)), dim3(256), args,
-                                  0, st, ev_start, ev_stop, 0);
-    }
-    hipLaunchKernelGGL(k_fold, dim3(grid1d(points, 256)), dim3(256), 0, st, p4, S, splits, points);
-    return hipGetLastError();
+    // Groups of splits per block.  From 32768 points on, one thread per point with 16 loads
+    // in flight already reads at the rate HBM delivers (128 splits x 32768 points 12.7 us, 4
+    // groups 12.8; 256 splits 20.9 against 21.7; 65536 points 12.2 against 13.0).  Below, its
+    // blocks are too few: 3700 points 16.5 us against 6.0 with 16 groups.  A group has at
+    // least one split.
+    if (points >= 32768 || splits < 4) return launch_fold_g<1>(p4, S, splits, points, st, ev_start, ev_stop);
+    if (points >= 8192 || splits < 16) return launch_fold_g<4>(p4, S, splits, points, st, ev_start, ev_stop);
+    return launch_fold_g<16>(p4, S, splits, points, st, ev_start, ev_stop);
 }
 
 hipError_t launch_finalize(const double* S, double* I, int n_dir, int n_omega, double C,
