@@ -1,6 +1,6 @@
 """The fixed-order FP64 folds at the edges of their groups: numbers of particle splits around
-the groups of one block and numbers of points on both sides of each dispatch line, against
-the FP64 oracle (gate 1e-4)."""
+the groups of one block, numbers of points on both sides of each dispatch line, and the
+tracked read-out's groups of particles, each against the FP64 oracle (gate 1e-4)."""
 import pytest
 
 import oracle
@@ -40,6 +40,16 @@ def test_fold_groups(rad, n, nx, ny, n_omega):
     g = rad.Grid(w.directions(), w.omega0, w.domega, w.n_omega, shape=w.shape, shape_len=w.shape_len, dt=w.dt)
     g.push_step(0.0, to_device(st, "f32"))
     assert_parity(g.spectrum(), reference(w, st), f"fold {n} particles, {nx * ny} x {n_omega}")
+
+
+@pytest.mark.parametrize("n,nx,ny,n_omega", [
+    (1, 3, 1, 37), (7, 3, 1, 37), (8, 3, 1, 37), (63, 3, 1, 37), (64, 3, 1, 37), (97, 3, 1, 37), (65, 16, 16, 128)])
+def test_tracked_read_out_groups(rad, n, nx, ny, n_omega):
+    w = workload(n, nx, ny, n_omega, 52)
+    st = w.steps()
+    tr = rad.Tracked(w.directions(), w.omega0, w.domega, w.n_omega, n, dt=w.dt)
+    tr.push_step(0.0, to_device(st, "f32"))
+    assert_parity(tr.spectrum(st["w"][0], w.shape, w.shape_len), reference(w, st), f"tracked {n} particles")
 
 
 # one to forty segments of one tile, and bunches of very different sizes in one batch
