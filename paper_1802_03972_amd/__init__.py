@@ -27,7 +27,9 @@ FIELDS = ("x", "y", "z", "bx", "by", "bz", "dbx", "dby", "dbz", "w")
 def _stream_handle(stream, device: int):
     import torch
     if stream is None:
-        stream = torch.cuda.current_stream(device)
+        # the handle alone: building a Stream object costs 1.5 us more on every call
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        return ctypes.c_void_p(raw(device) if raw else torch.cuda.current_stream(device).cuda_stream)
     if isinstance(stream, int):
         return ctypes.c_void_p(stream)
     return ctypes.c_void_p(stream.cuda_stream)

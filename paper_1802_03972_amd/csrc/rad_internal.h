@@ -120,8 +120,8 @@ hipError_t launch_finalize(const double* S, double* I, int n_dir, int n_omega, d
                            hipStream_t st);
 hipError_t launch_cartesian(const double* S, const double* dirs9, double* out, int n_dir,
                             int n_omega, hipStream_t st);
-hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t st);
-hipError_t launch_fill_int(int* p, int64_t n, int v, hipStream_t st);
+// Zeroes p[0 .. n) (16-byte aligned, n even; n = 0: nothing) and the error flag.
+hipError_t launch_reset(double* p, int64_t n, int* err, hipStream_t st);
 hipError_t launch_trig_probe(const float* in, float* out, int n, hipStream_t st);
 hipError_t launch_tracked_accumulate(const TrackedArgs& a, int dtype, bool direct, hipStream_t st);
 hipError_t launch_tracked_finalize(const double* T, const double* wts, const double* gk, const double* g3,

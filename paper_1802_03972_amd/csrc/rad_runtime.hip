@@ -160,15 +160,16 @@ struct rad_grid {
     float* d_part[2] = {nullptr, nullptr};
     int64_t part_splits = 0;
     int part_next = 0;
-    // Ordering hub of the writes of S: every single-push fold (run on the pushing stream),
-    // batched fold, reset and device read-out is chained into it; a call on another stream
-    // than the last write's waits for its last event.
-    hipStream_t fold_stream = nullptr;
-    hipEvent_t ev_fold_done[2] = {nullptr, nullptr};
-    hipStream_t fold_done_on[2] = {nullptr, nullptr};   // stream that orders the write each event marks
-    hipEvent_t ev_write = nullptr;   // end of a write of S on a caller's stream (reset)
-    bool fold_recorded[2] = {false, false};
-    int last_fold = -1;
+    // Ordering of the work on S and on the partial-sum buffers (order_after, mark_done).
+    struct Mark {
+        hipEvent_t own = nullptr;
+        hipEvent_t ev = nullptr;    // own, or the event that a launch stamped for another mark too
+        hipStream_t on = nullptr;   // stream that the marked work was issued on
+        bool set = false;           // something was marked
+        bool recorded = false;      // ev stands for it (on the null stream: recorded when asked for)
+    };
+    Mark part_read[2];              // the fold that last read each partial-sum buffer
+    Mark last_write;                // the last fold, batched fold, reset or device read-out of S
     int* d_err = nullptr;
     double* d_out = nullptr;
     float* d_g3 = nullptr;     // [n_dir][n_omega] for 3-D shapes
@@ -296,10 +297,9 @@ void free_grid(rad_grid* g)
     if (g->d_S) (void)hipFree(g->d_S);
     for (int b = 0; b < 2; ++b) {
         if (g->d_part[b]) (void)hipFree(g->d_part[b]);
-        if (g->ev_fold_done[b]) (void)hipEventDestroy(g->ev_fold_done[b]);
+        if (g->part_read[b].own) (void)hipEventDestroy(g->part_read[b].own);
     }
-    if (g->ev_write) (void)hipEventDestroy(g->ev_write);
-    if (g->fold_stream) (void)hipStreamDestroy(g->fold_stream);
+    if (g->last_write.own) (void)hipEventDestroy(g->last_write.own);
     if (g->d_err) (void)hipFree(g->d_err);
     if (g->d_out) (void)hipFree(g->d_out);
     if (g->d_g3) (void)hipFree(g->d_g3);
@@ -364,6 +364,34 @@ int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, Fn fn)
     return RAD_OK;
 }
 
+// Work marked on one stream is ordered before later work on another by an event; work on
+// the stream of the mark needs none.  On a caller's own stream the event is recorded when the
+// work is issued (the stream may be gone when somebody asks).  The null stream is always
+// there, so its event is recorded only when another stream asks: a program on the default
+// stream pays for no event (a record and the wait for it are 4 to 6 us of host time each, and
+// an event stamped by a fold left the GPU idle for 4.7 us before the next push's accumulate).
+hipError_t order_after(rad_grid::Mark& m, hipStream_t st)
+{
+    if (!m.set || m.on == st) return hipSuccess;
+    if (!m.recorded) {
+        const hipError_t e = hipEventRecord(m.ev, m.on);
+        if (e != hipSuccess) return e;
+        m.recorded = true;
+    }
+    return hipStreamWaitEvent(st, m.ev, 0);
+}
+
+// Everything issued on `st` so far is marked.  stamped: an event that the last launch on `st`
+// stamped (a caller's own stream only), or null to record the mark's own.
+hipError_t mark_done(rad_grid::Mark& m, hipStream_t st, hipEvent_t stamped = nullptr)
+{
+    m.on = st;
+    m.set = true;
+    m.recorded = st != nullptr;
+    m.ev = st && stamped ? stamped : m.own;
+    return m.recorded && !stamped ? hipEventRecord(m.ev, st) : hipSuccess;
+}
+
 // Accumulate particles [0, total) (step of element i is i / n_per_step, t = t0 + step*dt).
 int push_range(rad_grid* g, double t0, int64_t n_per_step, int64_t total, const rad_particles* p,
                hipStream_t st)
@@ -381,9 +409,8 @@ int push_range(rad_grid* g, double t0, int64_t n_per_step, int64_t total, const 
         const int b = g->part_next;
         g->part_next ^= 1;
         a.part = g->d_part[b];
-        // the fold that last read this buffer must be done before it is overwritten (stream
-        // order already guarantees it when that event was recorded on this stream)
-        if (g->fold_recorded[b] && g->fold_done_on[b] != st) RAD_HIP(hipStreamWaitEvent(st, g->ev_fold_done[b], 0));
+        // the fold that last read this buffer must be done before it is overwritten
+        RAD_HIP(order_after(g->part_read[b], st));
         hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr, e3 = nullptr;
         if (g->profiling && g->prof_count++ % g->prof_period == 0) {
             RAD_HIP(take_event(g, &e0));
@@ -398,49 +425,18 @@ int push_range(rad_grid* g, double t0, int64_t n_per_step, int64_t total, const 
         if (e != hipSuccess) return hip_fail(e, "accumulate launch");
         // The fold runs right after the accumulate on the caller's stream, so it has the
         // whole GPU for its few microseconds (beside the next push's accumulate it would
-        // trickle along in the few free wave slots).  It comes after every fold already
-        // issued for this grid, on whatever stream, and the grid's fold stream -- the
-        // ordering point of batched folds, resets and read-outs -- is chained behind it.
-        // The fold's completion event is stamped by the fold launch itself (no separate
-        // marker between this fold and the next push's accumulate: 0.4 % of the whole job
-        // for per-step pushes); a timed fold stamps its timing event and records it after.
-        if (g->last_fold >= 0 && g->fold_done_on[g->last_fold] != st)
-            RAD_HIP(hipStreamWaitEvent(st, g->ev_fold_done[g->last_fold], 0));
-        e = rad::launch_fold(g->d_part[b], g->d_S, (int)splits, count, st, e2, e3 ? e3 : g->ev_fold_done[b]);
+        // trickle along in the few free wave slots), and after every write of S already issued
+        // on another stream.  Where an event is needed (another stream than the null stream)
+        // the fold's launch stamps it, without a marker between this fold and the next push's
+        // accumulate; a timed fold stamps its timing event, and the mark is recorded after it.
+        RAD_HIP(order_after(g->last_write, st));
+        const hipEvent_t stamp = e3 || !st ? nullptr : g->part_read[b].own;
+        e = rad::launch_fold(g->d_part[b], g->d_S, (int)splits, count, st, e2, e3 ? e3 : stamp);
         if (e != hipSuccess) return hip_fail(e, "fold launch");
-        if (e3) RAD_HIP(hipEventRecord(g->ev_fold_done[b], st));
-        RAD_HIP(hipStreamWaitEvent(g->fold_stream, g->ev_fold_done[b], 0));
-        g->fold_done_on[b] = st;
-        g->fold_recorded[b] = true;
-        g->last_fold = b;
+        RAD_HIP(mark_done(g->part_read[b], st, stamp));
+        RAD_HIP(mark_done(g->last_write, st, st ? g->part_read[b].own : nullptr));
         return RAD_OK;
     });
-}
-
-// Make `st` wait for every fold already enqueued (the fold stream is in order, so the
-// last one suffices).  Every call that touches the accumulator S on `st` does this first.
-int after_folds(rad_grid* g, hipStream_t st)
-{
-    if (g->last_fold >= 0 && g->fold_done_on[g->last_fold] != st)
-        RAD_HIP(hipStreamWaitEvent(st, g->ev_fold_done[g->last_fold], 0));
-    return RAD_OK;
-}
-
-// S was just written (a batched fold, a reset) or read (a device read-out) on stream
-// `origin` up to `ev`, after every earlier fold: later folds, resets and read-outs must come
-// after it.  Chain the fold stream behind `ev` and move the last-fold mark there, owned by
-// `origin`: later calls on `origin` are ordered by the stream itself and skip the wait (a
-// wait on the fold stream's event costs a round trip through another hardware queue, about
-// 0.1 ms), calls on any other stream wait for the fold stream's event.
-int chain_fold_stream(rad_grid* g, hipEvent_t ev, hipStream_t origin)
-{
-    RAD_HIP(hipStreamWaitEvent(g->fold_stream, ev, 0));
-    const int k = g->last_fold >= 0 ? g->last_fold : 0;
-    RAD_HIP(hipEventRecord(g->ev_fold_done[k], g->fold_stream));
-    g->fold_done_on[k] = origin;
-    g->fold_recorded[k] = true;
-    g->last_fold = k;
-    return RAD_OK;
 }
 
 int read_err_flag(rad_grid* g, hipStream_t st, int* flag)
@@ -631,12 +627,11 @@ int rad_create_grid(rad_grid** out, const rad_grid_desc* d)
     }
     int rc = ensure_partials(g);
     if (rc) { free_grid(g); return rc; }
-    if (hipStreamCreateWithFlags(&g->fold_stream, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&g->ev_fold_done[0], hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&g->ev_fold_done[1], hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&g->ev_write, hipEventDisableTiming) != hipSuccess) {
+    if (hipEventCreateWithFlags(&g->part_read[0].own, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&g->part_read[1].own, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&g->last_write.own, hipEventDisableTiming) != hipSuccess) {
         free_grid(g);
-        return fail(RAD_ERR_DEVICE, "cannot create the grid's fold stream and events");
+        return fail(RAD_ERR_DEVICE, "cannot create the grid's events");
     }
     hipError_t e;
     if ((e = hipMemcpy(g->d_dirs9, dirs9.data(), dirs9.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess ||
@@ -645,8 +640,7 @@ int rad_create_grid(rad_grid** out, const rad_grid_desc* d)
         (!g3.empty() && (e = hipMemcpy(g->d_g3, g3.data(), g3.size() * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess) ||
         (!tb.bstep.empty() &&
          (e = hipMemcpy(g->d_bstep, tb.bstep.data(), tb.bstep.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess) ||
-        (e = rad::launch_fill(g->d_S, points * 4, 0.0, nullptr)) != hipSuccess ||
-        (e = rad::launch_fill_int(g->d_err, 1, 0, nullptr)) != hipSuccess ||
+        (e = rad::launch_reset(g->d_S, points * 4, g->d_err, nullptr)) != hipSuccess ||
         (e = hipDeviceSynchronize()) != hipSuccess) {
         free_grid(g);
         return hip_fail(e, "grid initialisation");
@@ -671,12 +665,11 @@ int rad_reset(rad_grid* g, void* stream)
     if (!g) return fail(RAD_ERR_INVALID_ARG, "grid is NULL");
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)stream;
-    if (int rc0 = after_folds(g, st)) return rc0;
-    hipError_t e = rad::launch_fill(g->d_S, (int64_t)g->n_dir * g->n_omega * 4, 0.0, st);
-    if (e == hipSuccess) e = rad::launch_fill_int(g->d_err, 1, 0, st);
-    if (e == hipSuccess) e = hipEventRecord(g->ev_write, st);
+    RAD_HIP(order_after(g->last_write, st));
+    hipError_t e = rad::launch_reset(g->d_S, (int64_t)g->n_dir * g->n_omega * 4, g->d_err, st);
+    if (e == hipSuccess) e = mark_done(g->last_write, st);
     if (e != hipSuccess) return hip_fail(e, "reset");
-    return chain_fold_stream(g, g->ev_write, st);
+    return RAD_OK;
 }
 
 int rad_push_step(rad_grid* g, double t, int64_t n_particles, const rad_particles* p, void* stream)
@@ -733,9 +726,7 @@ int rad_push_step_noalloc(rad_grid* g, double t, int64_t n_particles, const rad_
     const bool capturing = cap != hipStreamCaptureStatusNone;
     // every fold of this grid runs in issue order: the folds below come after every fold
     // already issued (on any stream), later folds, read-outs and resets after them
-    if (!capturing) {
-        if (int rc0 = after_folds(g, st)) return rc0;
-    }
+    if (!capturing) RAD_HIP(order_after(g->last_write, st));
     const LaunchShape ls = shape_of(g->tile, g->variant);
     const int nt = tiles_d(g) * tiles_w(g);
     AccArgs a{};
@@ -751,9 +742,8 @@ int rad_push_step_noalloc(rad_grid* g, double t, int64_t n_particles, const rad_
         return RAD_OK;
     });
     if (rc) return rc;
-    if (capturing) return RAD_OK;
-    RAD_HIP(hipEventRecord(g->ev_write, st));
-    return chain_fold_stream(g, g->ev_write, st);
+    if (!capturing) RAD_HIP(mark_done(g->last_write, st));
+    return RAD_OK;
 }
 
 int rad_spectrum_device(rad_grid* g, double* I_dev, void* stream)
@@ -761,13 +751,13 @@ int rad_spectrum_device(rad_grid* g, double* I_dev, void* stream)
     if (!g || !I_dev) return fail(RAD_ERR_INVALID_ARG, "grid and output must be non-NULL");
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)stream;
-    if (int rc0 = after_folds(g, st)) return rc0;
+    RAD_HIP(order_after(g->last_write, st));
     hipError_t e = rad::launch_finalize(g->d_S, I_dev, g->n_dir, g->n_omega, g->C, st);
     if (e != hipSuccess) return hip_fail(e, "finalize launch");
     // The read-out does not synchronise: later folds and resets, on any stream, must not
     // write S before it has been read, so the read-out becomes the grid's last-write mark.
-    RAD_HIP(hipEventRecord(g->ev_write, st));
-    return chain_fold_stream(g, g->ev_write, st);
+    RAD_HIP(mark_done(g->last_write, st));
+    return RAD_OK;
 }
 
 int rad_spectrum(rad_grid* g, double* I_host, void* stream)
@@ -775,7 +765,7 @@ int rad_spectrum(rad_grid* g, double* I_host, void* stream)
     if (!g || !I_host) return fail(RAD_ERR_INVALID_ARG, "grid and output must be non-NULL");
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)stream;
-    if (int rc0 = after_folds(g, st)) return rc0;
+    RAD_HIP(order_after(g->last_write, st));
     hipError_t e = rad::launch_finalize(g->d_S, g->d_out, g->n_dir, g->n_omega, g->C, st);
     if (e != hipSuccess) return hip_fail(e, "finalize launch");
     int flag = 0;
@@ -793,7 +783,7 @@ int rad_spectrum_complex(rad_grid* g, double* S_host, void* stream)
     if (!g || !S_host) return fail(RAD_ERR_INVALID_ARG, "grid and output must be non-NULL");
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)stream;
-    if (int rc0 = after_folds(g, st)) return rc0;
+    RAD_HIP(order_after(g->last_write, st));
     hipError_t e = rad::launch_cartesian(g->d_S, g->d_dirs9, g->d_out, g->n_dir, g->n_omega, st);
     if (e != hipSuccess) return hip_fail(e, "cartesian launch");
     int flag = 0;
@@ -816,7 +806,7 @@ int rad_get_state(rad_grid* g, double* state_host, void* stream)
     if (!g || !state_host) return fail(RAD_ERR_INVALID_ARG, "grid and state must be non-NULL");
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)stream;
-    if (int rc0 = after_folds(g, st)) return rc0;
+    RAD_HIP(order_after(g->last_write, st));
     int flag = 0;
     int rc = read_err_flag(g, st, &flag);
     if (rc) return rc;
@@ -831,9 +821,9 @@ int rad_set_state(rad_grid* g, const double* state_host, void* stream)
     if (!g || !state_host) return fail(RAD_ERR_INVALID_ARG, "grid and state must be non-NULL");
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)stream;
-    if (int rc0 = after_folds(g, st)) return rc0;
+    RAD_HIP(order_after(g->last_write, st));
     RAD_HIP(hipMemcpyAsync(g->d_S, state_host, rad_state_size(g) * sizeof(double), hipMemcpyHostToDevice, st));
-    hipError_t e = rad::launch_fill_int(g->d_err, 1, 0, st);
+    hipError_t e = rad::launch_reset(nullptr, 0, g->d_err, st);
     if (e != hipSuccess) return hip_fail(e, "set_state");
     RAD_HIP(hipStreamSynchronize(st));
     return RAD_OK;
@@ -1175,7 +1165,7 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
         for (const auto& in : info) {
             if (std::find(seen.begin(), seen.end(), in.grid) != seen.end()) continue;
             seen.push_back(in.grid);
-            if (int rc = after_folds(in.grid, st)) return rc;
+            RAD_HIP(order_after(in.grid->last_write, st));
         }
     }
     int64_t I = 0;
@@ -1187,7 +1177,7 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
     const int TD = rad::tile_dirs(ls), TO = rad::tile_omegas(ls);
     const int R_target = std::max(1, b->cus * btile.wg_per_cu);
     const int64_t per_launch = (int64_t)R_target * (kMaxPerWorkgroup / rad::kChunk);
-    hipEvent_t last_done = nullptr;
+    bool launched = false;
     for (int64_t L0 = 0; L0 < I; L0 += per_launch) {
         const int64_t L1 = std::min(I, L0 + per_launch);
         const int R = (int)std::min<int64_t>(R_target, L1 - L0);
@@ -1340,17 +1330,17 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
         }
         RAD_HIP(hipEventRecord(sl.done, st));
         sl.used = true;
-        last_done = sl.done;
+        launched = true;
     }
     // Later single-grid folds (on whatever stream pushes them), resets and read-outs must
-    // come after this batch's fold: chain each grid's fold stream behind it.
-    if (last_done) {
+    // come after this batch's fold.
+    if (launched) {
         std::vector<rad_grid*> seen;
         for (const auto& in : info) {
             rad_grid* g = in.grid;
             if (std::find(seen.begin(), seen.end(), g) != seen.end()) continue;
             seen.push_back(g);
-            if (int rc = chain_fold_stream(g, last_done, st)) return rc;
+            RAD_HIP(mark_done(g->last_write, st));
         }
     }
     return RAD_OK;
@@ -1507,8 +1497,7 @@ extern "C" int rad_tracked_create(rad_tracked** out, const rad_grid_desc* d, int
     hipError_t e;
     if ((e = hipMemcpy(tr->d_dirs9, tb.dirs9.data(), tb.dirs9.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(tr->d_omega, tb.om.data(), tb.om.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = rad::launch_fill(tr->d_T, (int64_t)(tbytes / sizeof(double)), 0.0, nullptr)) != hipSuccess ||
-        (e = rad::launch_fill_int(tr->d_err, 1, 0, nullptr)) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess) {
+        (e = rad::launch_reset(tr->d_T, (int64_t)(tbytes / sizeof(double)), tr->d_err, nullptr)) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess) {
         free_tracked(tr);
         return hip_fail(e, "tracked initialisation");
     }
@@ -1532,8 +1521,7 @@ extern "C" int rad_tracked_reset(rad_tracked* tr, void* stream)
     if (!tr) return fail(RAD_ERR_INVALID_ARG, "tracked is NULL");
     DeviceGuard dg(tr->device);
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = rad::launch_fill(tr->d_T, tr->n_particles * tr->n_dir * tr->n_omega * 4, 0.0, st);
-    if (e == hipSuccess) e = rad::launch_fill_int(tr->d_err, 1, 0, st);
+    hipError_t e = rad::launch_reset(tr->d_T, tr->n_particles * tr->n_dir * tr->n_omega * 4, tr->d_err, st);
     if (e != hipSuccess) return hip_fail(e, "tracked reset");
     return RAD_OK;
 }
