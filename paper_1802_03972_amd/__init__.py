@@ -181,7 +181,7 @@ class Grid:
         out = np.empty((self.n_dir, self.n_omega, 3, 2), np.float64)
         _lib.check(_lib.lib().rad_spectrum_complex(self._h, out.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
                                                    _stream_handle(stream, self.device)))
-        return out[..., 0] + 1j * out[..., 1]
+        return out.view(np.complex128)[..., 0]
 
     # ------------------------------------------------------------------ state
     def state_size(self) -> int:

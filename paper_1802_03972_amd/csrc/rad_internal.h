@@ -116,16 +116,18 @@ hipError_t prepare_accumulate_batch(int dtype, int precision, const LaunchShape&
 // with different plans; the grid is sized for max_jobs.
 hipError_t launch_fold_batch(const int32_t* n_jobs_dev, const FoldJob* jobs, int max_jobs,
                              const int32_t* seg_list, const float* seg_part, int td, int to, hipStream_t st);
-hipError_t launch_finalize(const double* S, double* I, int n_dir, int n_omega, double C,
-                           hipStream_t st);
-hipError_t launch_cartesian(const double* S, const double* dirs9, double* out, int n_dir,
-                            int n_omega, hipStream_t st);
+// Read-outs.  The result and flag_out (may be null: the data-error flag *err) may be
+// page-locked host memory.
+hipError_t launch_finalize(const double* S, double* I, int n_dir, int n_omega, double C, const int* err,
+                           int* flag_out, hipStream_t st);
+hipError_t launch_cartesian(const double* S, const double* dirs9, double* out, int n_dir, int n_omega, const int* err,
+                            int* flag_out, hipStream_t st);
 // Zeroes p[0 .. n) (16-byte aligned, n even; n = 0: nothing) and the error flag.
 hipError_t launch_reset(double* p, int64_t n, int* err, hipStream_t st);
 hipError_t launch_trig_probe(const float* in, float* out, int n, hipStream_t st);
 hipError_t launch_tracked_accumulate(const TrackedArgs& a, int dtype, bool direct, hipStream_t st);
 hipError_t launch_tracked_finalize(const double* T, const double* wts, const double* gk, const double* g3,
-                                   int64_t n_particles, int n_dir, int n_omega, double C, double* I,
-                                   hipStream_t st);
+                                   int64_t n_particles, int n_dir, int n_omega, double C, double* I, const int* err,
+                                   int* flag_out, hipStream_t st);
 
 }  // namespace rad

@@ -239,7 +239,7 @@ template <int G>
 __global__ void __launch_bounds__(256) k_tracked_finalize(const double* __restrict__ T, const double* __restrict__ wts,
                                                           const double* __restrict__ gk, const double* __restrict__ g3,
                                                           int64_t n_particles, int n_dir, int n_omega, double C,
-                                                          double* __restrict__ I)
+                                                          double* __restrict__ I, const int* err, int* flag_out)
 {
     constexpr int PT = 256 / G;
     constexpr int U = 4;                          // particles in flight per thread
@@ -285,6 +285,7 @@ __global__ void __launch_bounds__(256) k_tracked_finalize(const double* __restri
         }
     }
     if (q == 0 && i < points) I[(int64_t)d * n_omega + k] = C * (s0 * s0 + s1 * s1 + s2 * s2 + s3 * s3);
+    if (flag_out && blockIdx.x == 0 && threadIdx.x == 0) *flag_out = *err;
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -412,30 +413,76 @@ __global__ void __launch_bounds__(256) k_fold_batch(const int32_t* __restrict__ 
     }
 }
 
-// I[d][k] = C * (|S1|^2 + |S2|^2), S layout [omega][dir][4].
-__global__ void k_finalize(const double* __restrict__ S, double* __restrict__ I, int n_dir,
-                           int n_omega, double C)
+// Read-out kernels: a block of 256 threads takes 16 x 16 (direction, frequency) points, one
+// per thread.  S is [omega][dir] and the results are [dir][omega], so the points are read with
+// consecutive threads on consecutive directions (512 B a row) and written through LDS with
+// consecutive threads on consecutive frequencies: full lines also where the result is
+// page-locked host memory.  flag_out (may be null) receives the data-error flag.
+constexpr int kOutTile = 16;
+
+struct OutPoint {
+    int d, k;      // the thread's point when reading S: consecutive directions
+    bool in;
+    int d0, k0;    // the block's first point
+};
+
+__device__ __forceinline__ OutPoint out_point(int n_dir, int n_omega)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)n_dir * n_omega) return;
-    const int d = (int)(i / n_omega), k = (int)(i % n_omega);
-    const double* s = S + ((int64_t)k * n_dir + d) * 4;
-    I[i] = C * (s[0] * s[0] + s[1] * s[1] + s[2] * s[2] + s[3] * s[3]);
+    const int tiles_k = (n_omega + kOutTile - 1) / kOutTile;
+    OutPoint o;
+    o.d0 = (int)(blockIdx.x / tiles_k) * kOutTile;
+    o.k0 = (int)(blockIdx.x % tiles_k) * kOutTile;
+    o.d = o.d0 + threadIdx.x % kOutTile;
+    o.k = o.k0 + threadIdx.x / kOutTile;
+    o.in = o.d < n_dir && o.k < n_omega;
+    return o;
+}
+
+// I[d][k] = C * (|S1|^2 + |S2|^2), S layout [omega][dir][4].
+__global__ void __launch_bounds__(256) k_finalize(const double* __restrict__ S, double* __restrict__ I, int n_dir,
+                                                  int n_omega, double C, const int* err, int* flag_out)
+{
+    __shared__ double tile[kOutTile][kOutTile + 1];
+    const OutPoint o = out_point(n_dir, n_omega);
+    const int t = threadIdx.x;
+    if (o.in) {
+        const double2* s = reinterpret_cast<const double2*>(S) + 2 * ((int64_t)o.k * n_dir + o.d);
+        const double2 a = s[0], b = s[1];
+        tile[t / kOutTile][t % kOutTile] = C * (a.x * a.x + a.y * a.y + b.x * b.x + b.y * b.y);
+    }
+    __syncthreads();
+    const int k = o.k0 + t % kOutTile, d = o.d0 + t / kOutTile;
+    if (d < n_dir && k < n_omega) I[(int64_t)d * n_omega + k] = tile[t % kOutTile][t / kOutTile];
+    if (flag_out && blockIdx.x == 0 && t == 0) *flag_out = *err;
 }
 
 // Cartesian complex spectrum out[((d*n_omega + k)*3 + c)*2 + {re, im}] = e1_c S1 + e2_c S2.
-__global__ void k_cartesian(const double* __restrict__ S, const double* __restrict__ dirs9,
-                            double* __restrict__ out, int n_dir, int n_omega)
+__global__ void __launch_bounds__(256) k_cartesian(const double* __restrict__ S, const double* __restrict__ dirs9,
+                                                   double* __restrict__ out, int n_dir, int n_omega, const int* err,
+                                                   int* flag_out)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)n_dir * n_omega) return;
-    const int d = (int)(i / n_omega), k = (int)(i % n_omega);
-    const double* s = S + ((int64_t)k * n_dir + d) * 4;
-    const double* e = dirs9 + 9 * d;
-    for (int c = 0; c < 3; ++c) {
-        out[(i * 3 + c) * 2 + 0] = e[3 + c] * s[0] + e[6 + c] * s[2];
-        out[(i * 3 + c) * 2 + 1] = e[3 + c] * s[1] + e[6 + c] * s[3];
+    constexpr int R = 6 * kOutTile;               // values of one direction of the tile
+    __shared__ double tile[kOutTile][R + 1];
+    const OutPoint o = out_point(n_dir, n_omega);
+    const int t = threadIdx.x;
+    if (o.in) {
+        const double2* s = reinterpret_cast<const double2*>(S) + 2 * ((int64_t)o.k * n_dir + o.d);
+        const double2 a = s[0], b = s[1];
+        const double* e = dirs9 + 9 * o.d;
+        double* row = &tile[t % kOutTile][6 * (t / kOutTile)];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            row[2 * c + 0] = e[3 + c] * a.x + e[6 + c] * b.x;
+            row[2 * c + 1] = e[3 + c] * a.y + e[6 + c] * b.y;
+        }
     }
+    __syncthreads();
+    const int live = 6 * (n_omega - o.k0 < kOutTile ? n_omega - o.k0 : kOutTile);
+    for (int i = t; i < kOutTile * R; i += 256) {
+        const int d = o.d0 + i / R, r = i % R;
+        if (d < n_dir && r < live) out[((int64_t)d * n_omega + o.k0) * 6 + r] = tile[i / R][r];
+    }
+    if (flag_out && blockIdx.x == 0 && t == 0) *flag_out = *err;
 }
 
 // Zeroes n2 pairs of doubles and the error flag in one launch (the flag's own launch cost a
@@ -510,20 +557,25 @@ hipError_t launch_fold(const float* part, double* S, int splits, int64_t count, 
     return launch_fold_g<16>(p4, S, splits, points, st, ev_start, ev_stop);
 }
 
-hipError_t launch_finalize(const double* S, double* I, int n_dir, int n_omega, double C,
-                           hipStream_t st)
+namespace {
+
+unsigned out_blocks(int n_dir, int n_omega) { return grid1d(n_dir, kOutTile) * grid1d(n_omega, kOutTile); }
+
+}  // namespace
+
+hipError_t launch_finalize(const double* S, double* I, int n_dir, int n_omega, double C, const int* err,
+                           int* flag_out, hipStream_t st)
 {
-    const int64_t n = (int64_t)n_dir * n_omega;
-    hipLaunchKernelGGL(k_finalize, dim3(grid1d(n, 256)), dim3(256), 0, st, S, I, n_dir, n_omega, C);
+    hipLaunchKernelGGL(k_finalize, dim3(out_blocks(n_dir, n_omega)), dim3(256), 0, st, S, I, n_dir, n_omega, C, err,
+                       flag_out);
     return hipGetLastError();
 }
 
-hipError_t launch_cartesian(const double* S, const double* dirs9, double* out, int n_dir,
-                            int n_omega, hipStream_t st)
+hipError_t launch_cartesian(const double* S, const double* dirs9, double* out, int n_dir, int n_omega, const int* err,
+                            int* flag_out, hipStream_t st)
 {
-    const int64_t n = (int64_t)n_dir * n_omega;
-    hipLaunchKernelGGL(k_cartesian, dim3(grid1d(n, 256)), dim3(256), 0, st, S, dirs9, out, n_dir,
-                       n_omega);
+    hipLaunchKernelGGL(k_cartesian, dim3(out_blocks(n_dir, n_omega)), dim3(256), 0, st, S, dirs9, out, n_dir, n_omega,
+                       err, flag_out);
     return hipGetLastError();
 }
 
@@ -562,13 +614,13 @@ hipError_t launch_tracked_accumulate(const TrackedArgs& a, int dtype, bool direc
 }
 
 hipError_t launch_tracked_finalize(const double* T, const double* wts, const double* gk, const double* g3,
-                                   int64_t n_particles, int n_dir, int n_omega, double C, double* I,
-                                   hipStream_t st)
+                                   int64_t n_particles, int n_dir, int n_omega, double C, double* I, const int* err,
+                                   int* flag_out, hipStream_t st)
 {
     const int64_t points = (int64_t)n_dir * n_omega;
     auto go = [&](auto kern, int groups) {
         hipLaunchKernelGGL(kern, dim3(grid1d(points, 256 / groups)), dim3(256), 0, st, T, wts, gk, g3, n_particles,
-                           n_dir, n_omega, C, I);
+                           n_dir, n_omega, C, I, err, flag_out);
         return hipGetLastError();
     };
     // Groups of particles per block: as few as give the chip 4096 waves (16 per CU).

@@ -126,6 +126,90 @@ int scratch_setup(int dev)
     return RAD_OK;
 }
 
+// ---- page-locked host buffers of the read-outs ------------------------------------------
+// A host read-out's kernel writes its result and the data-error flag into a page-locked buffer,
+// the call waits for the stream once and copies the result on.  Through device memory it takes
+// a wait for the flag and one for a copy into pageable memory: 482 points 48 us against 15,
+// 32768 points 62 against 25, 1048576 points (8.4 MB) 517 against 438; the line below is where
+// keeping the buffers costs more memory than the 15 % are worth.  The buffers are shared by all
+// grids and threads, are held only during a call, at most kStagesKept are kept, and all are
+// given back when the last grid is destroyed.
+constexpr size_t kStageHeader = 256;      // the flag's place before the result
+constexpr size_t kMaxStageBytes = (size_t)8 << 20;
+constexpr size_t kStagesKept = 8;
+
+class StagePool {
+public:
+    struct Stage {
+        unsigned char* host = nullptr;
+        unsigned char* dev = nullptr;     // the same memory as the device addresses it
+        size_t bytes = 0;
+        int* flag() const { return reinterpret_cast<int*>(host); }
+    };
+    void retain()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        ++users_;
+    }
+    void drop()
+    {
+        std::vector<Stage> gone;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (--users_ == 0) gone.swap(free_);
+        }
+        for (const Stage& s : gone) (void)hipHostFree(s.host);
+    }
+    hipError_t take(size_t bytes, Stage* out)
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            auto best = free_.end();
+            for (auto it = free_.begin(); it != free_.end(); ++it)
+                if (it->bytes >= bytes && (best == free_.end() || it->bytes < best->bytes)) best = it;
+            if (best != free_.end()) {
+                *out = *best;
+                free_.erase(best);
+                return hipSuccess;
+            }
+        }
+        Stage s;
+        s.bytes = 64 * 1024;
+        while (s.bytes < bytes) s.bytes *= 2;
+        hipError_t e = hipHostMalloc((void**)&s.host, s.bytes, hipHostMallocPortable | hipHostMallocMapped);
+        if (e != hipSuccess) return e;
+        e = hipHostGetDevicePointer((void**)&s.dev, s.host, 0);
+        if (e != hipSuccess) {
+            (void)hipHostFree(s.host);
+            return e;
+        }
+        *out = s;
+        return hipSuccess;
+    }
+    void give_back(const Stage& s)
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (users_ > 0 && free_.size() < kStagesKept) {
+                free_.push_back(s);
+                return;
+            }
+        }
+        (void)hipHostFree(s.host);
+    }
+
+private:
+    std::mutex mu_;
+    std::vector<Stage> free_;
+    int64_t users_ = 0;
+};
+
+StagePool& stages()
+{
+    static StagePool* pool = new StagePool;   // outlives every grid, also at process end
+    return *pool;
+}
+
 struct DeviceGuard {
     int prev = -1;
     explicit DeviceGuard(int dev)
@@ -175,6 +259,7 @@ struct rad_grid {
     float* d_g3 = nullptr;     // [n_dir][n_omega] for 3-D shapes
     double* d_bstep = nullptr; // per-block spacing of a piecewise-uniform frequency list
     int variant = 0;           // rad::kVarDirect | rad::kVarShape3
+    bool counted = false;      // among the users of the read-out buffers
     // kernel timing (rad_profile_*)
     bool profiling = false;
     int64_t prof_period = 1;    // time every prof_period-th accumulate launch
@@ -304,6 +389,7 @@ void free_grid(rad_grid* g)
     if (g->d_out) (void)hipFree(g->d_out);
     if (g->d_g3) (void)hipFree(g->d_g3);
     if (g->d_bstep) (void)hipFree(g->d_bstep);
+    if (g->counted) stages().drop();
     delete g;
 }
 
@@ -442,6 +528,37 @@ int push_range(rad_grid* g, double t0, int64_t n_per_step, int64_t total, const 
 int read_err_flag(rad_grid* g, hipStream_t st, int* flag)
 {
     RAD_HIP(hipMemcpyAsync(flag, g->d_err, sizeof(int), hipMemcpyDeviceToHost, st));
+    RAD_HIP(hipStreamSynchronize(st));
+    return RAD_OK;
+}
+
+const char* const kBadData = "device detected invalid particle data (non-finite, N < 0 or 1 - beta.n <= 0)";
+
+// Host read-out of `count` doubles: launch(result, flag, stream) writes them and the data-error
+// flag.  Up to kMaxStageBytes they go straight to page-locked memory; larger ones through the
+// grid's device buffer.  Nothing is written to `out` when the flag is set.
+template <typename Launch>
+int read_out(rad_grid* g, double* out, size_t count, hipStream_t st, Launch launch)
+{
+    RAD_HIP(order_after(g->last_write, st));
+    const size_t bytes = count * sizeof(double);
+    StagePool::Stage sg;
+    if (bytes + kStageHeader <= kMaxStageBytes && stages().take(bytes + kStageHeader, &sg) == hipSuccess) {
+        hipError_t e = launch(reinterpret_cast<double*>(sg.dev + kStageHeader), reinterpret_cast<int*>(sg.dev), st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        // a buffer that a kernel may still write to is not handed on
+        if (e != hipSuccess) return hip_fail(e, "read-out");
+        const bool bad = *sg.flag() != 0;
+        if (!bad) std::memcpy(out, sg.host + kStageHeader, bytes);
+        stages().give_back(sg);
+        return bad ? fail(RAD_ERR_BAD_DATA, "%s", kBadData) : RAD_OK;
+    }
+    const hipError_t e = launch(g->d_out, nullptr, st);
+    if (e != hipSuccess) return hip_fail(e, "read-out launch");
+    int flag = 0;
+    if (int rc = read_err_flag(g, st, &flag)) return rc;
+    if (flag) return fail(RAD_ERR_BAD_DATA, "%s", kBadData);
+    RAD_HIP(hipMemcpyAsync(out, g->d_out, bytes, hipMemcpyDeviceToHost, st));
     RAD_HIP(hipStreamSynchronize(st));
     return RAD_OK;
 }
@@ -645,6 +762,8 @@ int rad_create_grid(rad_grid** out, const rad_grid_desc* d)
         free_grid(g);
         return hip_fail(e, "grid initialisation");
     }
+    stages().retain();
+    g->counted = true;
     *out = g;
     return RAD_OK;
 }
@@ -752,7 +871,7 @@ int rad_spectrum_device(rad_grid* g, double* I_dev, void* stream)
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)stream;
     RAD_HIP(order_after(g->last_write, st));
-    hipError_t e = rad::launch_finalize(g->d_S, I_dev, g->n_dir, g->n_omega, g->C, st);
+    hipError_t e = rad::launch_finalize(g->d_S, I_dev, g->n_dir, g->n_omega, g->C, g->d_err, nullptr, st);
     if (e != hipSuccess) return hip_fail(e, "finalize launch");
     // The read-out does not synchronise: later folds and resets, on any stream, must not
     // write S before it has been read, so the read-out becomes the grid's last-write mark.
@@ -764,36 +883,18 @@ int rad_spectrum(rad_grid* g, double* I_host, void* stream)
 {
     if (!g || !I_host) return fail(RAD_ERR_INVALID_ARG, "grid and output must be non-NULL");
     DeviceGuard dg(g->device);
-    hipStream_t st = (hipStream_t)stream;
-    RAD_HIP(order_after(g->last_write, st));
-    hipError_t e = rad::launch_finalize(g->d_S, g->d_out, g->n_dir, g->n_omega, g->C, st);
-    if (e != hipSuccess) return hip_fail(e, "finalize launch");
-    int flag = 0;
-    int rc = read_err_flag(g, st, &flag);
-    if (rc) return rc;
-    if (flag) return fail(RAD_ERR_BAD_DATA, "device detected invalid particle data (non-finite, N < 0 or 1 - beta.n <= 0)");
-    RAD_HIP(hipMemcpyAsync(I_host, g->d_out, (size_t)g->n_dir * g->n_omega * sizeof(double),
-                           hipMemcpyDeviceToHost, st));
-    RAD_HIP(hipStreamSynchronize(st));
-    return RAD_OK;
+    return read_out(g, I_host, (size_t)g->n_dir * g->n_omega, (hipStream_t)stream, [&](double* out, int* flag_out, hipStream_t st) {
+        return rad::launch_finalize(g->d_S, out, g->n_dir, g->n_omega, g->C, g->d_err, flag_out, st);
+    });
 }
 
 int rad_spectrum_complex(rad_grid* g, double* S_host, void* stream)
 {
     if (!g || !S_host) return fail(RAD_ERR_INVALID_ARG, "grid and output must be non-NULL");
     DeviceGuard dg(g->device);
-    hipStream_t st = (hipStream_t)stream;
-    RAD_HIP(order_after(g->last_write, st));
-    hipError_t e = rad::launch_cartesian(g->d_S, g->d_dirs9, g->d_out, g->n_dir, g->n_omega, st);
-    if (e != hipSuccess) return hip_fail(e, "cartesian launch");
-    int flag = 0;
-    int rc = read_err_flag(g, st, &flag);
-    if (rc) return rc;
-    if (flag) return fail(RAD_ERR_BAD_DATA, "device detected invalid particle data");
-    RAD_HIP(hipMemcpyAsync(S_host, g->d_out, (size_t)g->n_dir * g->n_omega * 6 * sizeof(double),
-                           hipMemcpyDeviceToHost, st));
-    RAD_HIP(hipStreamSynchronize(st));
-    return RAD_OK;
+    return read_out(g, S_host, (size_t)g->n_dir * g->n_omega * 6, (hipStream_t)stream, [&](double* out, int* flag_out, hipStream_t st) {
+        return rad::launch_cartesian(g->d_S, g->d_dirs9, out, g->n_dir, g->n_omega, g->d_err, flag_out, st);
+    });
 }
 
 size_t rad_state_size(const rad_grid* g)
@@ -1452,9 +1553,9 @@ struct rad_tracked {
     double* d_dirs9 = nullptr;
     double* d_omega = nullptr;
     double* d_T = nullptr;
-    double* d_w = nullptr;
-    double* d_g = nullptr;     // n_dir * n_omega shape factors of the last read-out
+    double* d_wg = nullptr;    // n_particles weights, then up to n_dir * n_omega shape factors
     double* d_I = nullptr;
+    bool counted = false;      // among the users of the read-out buffers
     int* d_err = nullptr;
 };
 
@@ -1464,9 +1565,10 @@ void free_tracked(rad_tracked* tr)
 {
     if (!tr) return;
     DeviceGuard dg(tr->device);
-    for (double* p : {tr->d_dirs9, tr->d_omega, tr->d_T, tr->d_w, tr->d_g, tr->d_I})
+    for (double* p : {tr->d_dirs9, tr->d_omega, tr->d_T, tr->d_wg, tr->d_I})
         if (p) (void)hipFree(p);
     if (tr->d_err) (void)hipFree(tr->d_err);
+    if (tr->counted) stages().drop();
     delete tr;
 }
 
@@ -1503,8 +1605,7 @@ extern "C" int rad_tracked_create(rad_tracked** out, const rad_grid_desc* d, int
     if (hipMalloc(&tr->d_dirs9, tb.dirs9.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&tr->d_omega, tb.om.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&tr->d_T, tbytes) != hipSuccess ||
-        hipMalloc(&tr->d_w, (size_t)n_particles * sizeof(double)) != hipSuccess ||
-        hipMalloc(&tr->d_g, (size_t)points * sizeof(double)) != hipSuccess ||
+        hipMalloc(&tr->d_wg, ((size_t)n_particles + points) * sizeof(double)) != hipSuccess ||
         hipMalloc(&tr->d_I, (size_t)points * sizeof(double)) != hipSuccess ||
         hipMalloc(&tr->d_err, sizeof(int)) != hipSuccess) {
         free_tracked(tr);
@@ -1517,6 +1618,8 @@ extern "C" int rad_tracked_create(rad_tracked** out, const rad_grid_desc* d, int
         free_tracked(tr);
         return hip_fail(e, "tracked initialisation");
     }
+    stages().retain();
+    tr->counted = true;
     *out = tr;
     return RAD_OK;
 }
@@ -1608,21 +1711,49 @@ extern "C" int rad_tracked_spectrum(rad_tracked* tr, const double* weights_host,
     DeviceGuard dg(tr->device);
     hipStream_t st = (hipStream_t)stream;
     const bool s3 = is_shape3(shape);
-    std::vector<double> g(s3 ? (size_t)tr->n_dir * tr->n_omega : (size_t)tr->n_omega);
-    for (int d = 0; d < (s3 ? tr->n_dir : 1); ++d)
-        for (int k = 0; k < tr->n_omega; ++k)
-            g[(size_t)d * tr->n_omega + k] = s3 ? shape_factor3(shape, shape_len, tr->dirs.data() + 3 * d, tr->om[k])
-                                                : shape_factor(shape, shape_len, tr->om[k]);
-    RAD_HIP(hipMemcpyAsync(tr->d_g, g.data(), g.size() * sizeof(double), hipMemcpyHostToDevice, st));
-    RAD_HIP(hipMemcpyAsync(tr->d_w, weights_host, (size_t)tr->n_particles * sizeof(double), hipMemcpyHostToDevice, st));
-    hipError_t e = rad::launch_tracked_finalize(tr->d_T, tr->d_w, s3 ? nullptr : tr->d_g, s3 ? tr->d_g : nullptr,
-                                                tr->n_particles, tr->n_dir, tr->n_omega, tr->C, tr->d_I, st);
+    // weights, then the shape factors, as the device buffer holds them
+    const size_t points = (size_t)tr->n_dir * tr->n_omega, n_g = s3 ? points : (size_t)tr->n_omega;
+    const size_t in_bytes = ((size_t)tr->n_particles + n_g) * sizeof(double), out_bytes = points * sizeof(double);
+    auto inputs = [&](double* dst) {
+        std::memcpy(dst, weights_host, (size_t)tr->n_particles * sizeof(double));
+        double* g = dst + tr->n_particles;
+        for (int d = 0; d < (s3 ? tr->n_dir : 1); ++d)
+            for (int k = 0; k < tr->n_omega; ++k)
+                g[(size_t)d * tr->n_omega + k] = s3 ? shape_factor3(shape, shape_len, tr->dirs.data() + 3 * d, tr->om[k])
+                                                    : shape_factor(shape, shape_len, tr->om[k]);
+    };
+    const double* d_g = tr->d_wg + tr->n_particles;
+    auto launch = [&](double* out, int* flag_out) {
+        return rad::launch_tracked_finalize(tr->d_T, tr->d_wg, s3 ? nullptr : d_g, s3 ? d_g : nullptr, tr->n_particles,
+                                            tr->n_dir, tr->n_omega, tr->C, out, tr->d_err, flag_out, st);
+    };
+    // Up to kMaxStageBytes the inputs leave from one page-locked buffer in one copy, and the
+    // flag and the result come back in it; the result by way of device memory, since its
+    // writes are single values (see k_tracked_finalize).
+    StagePool::Stage sg;
+    const size_t in_place = kStageHeader + (out_bytes + 255) / 256 * 256;
+    if (in_place + in_bytes <= kMaxStageBytes && stages().take(in_place + in_bytes, &sg) == hipSuccess) {
+        inputs(reinterpret_cast<double*>(sg.host + in_place));
+        hipError_t e = hipMemcpyAsync(tr->d_wg, sg.host + in_place, in_bytes, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = launch(tr->d_I, reinterpret_cast<int*>(sg.dev));
+        if (e == hipSuccess) e = hipMemcpyAsync(sg.host + kStageHeader, tr->d_I, out_bytes, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return hip_fail(e, "tracked read-out");
+        const bool bad = *sg.flag() != 0;
+        if (!bad) std::memcpy(I_host, sg.host + kStageHeader, out_bytes);
+        stages().give_back(sg);
+        return bad ? fail(RAD_ERR_BAD_DATA, "%s", kBadData) : RAD_OK;
+    }
+    std::vector<double> in((size_t)tr->n_particles + n_g);
+    inputs(in.data());
+    RAD_HIP(hipMemcpyAsync(tr->d_wg, in.data(), in_bytes, hipMemcpyHostToDevice, st));
+    const hipError_t e = launch(tr->d_I, nullptr);
     if (e != hipSuccess) return hip_fail(e, "tracked finalize launch");
     int flag = 0;
     RAD_HIP(hipMemcpyAsync(&flag, tr->d_err, sizeof(int), hipMemcpyDeviceToHost, st));
     RAD_HIP(hipStreamSynchronize(st));
-    if (flag) return fail(RAD_ERR_BAD_DATA, "device detected invalid particle data");
-    RAD_HIP(hipMemcpyAsync(I_host, tr->d_I, (size_t)tr->n_dir * tr->n_omega * sizeof(double), hipMemcpyDeviceToHost, st));
+    if (flag) return fail(RAD_ERR_BAD_DATA, "%s", kBadData);
+    RAD_HIP(hipMemcpyAsync(I_host, tr->d_I, out_bytes, hipMemcpyDeviceToHost, st));
     RAD_HIP(hipStreamSynchronize(st));
     return RAD_OK;
 }
