@@ -46,14 +46,20 @@ namespace rad {
 namespace {
 
 
-// Accumulate chunks [c_begin, c_end) of `j` into the tile (td, tw) and write the FP32
-// partial tile: element (omega o, direction d) of the tile goes to out[o * row + d] (as
-// (S1r, S1i, S2r, S2i)) when it lies inside the grid.  Every thread of the workgroup must
-// call this with the same arguments; LDS is reused chunk by chunk.
-template <typename InT, int PREC, int W, int DPW, int V>
-__device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, int64_t c_begin,
-                                                 int64_t c_end, float4* __restrict__ out, int row,
-                                                 float4* smem4)
+// Accumulate particles [p_begin, p_end) of `j` into the tile (td, tw), `chunk` (at most kChunk)
+// at a time, and write the FP32 partial tile: element (omega o, direction d) of the tile goes
+// to out[o * row + d] (as (S1r, S1i, S2r, S2i)) when it lies inside the grid.  Every thread of
+// the workgroup must call this with the same arguments; LDS is reused chunk by chunk.
+//
+// KSPLIT: the workgroup's waves are `groups` (a power of two) groups that cover the tile once
+// each and take every groups-th particle of a chunk; their sums are added through LDS at the
+// end.  A push too small for the chip's waves is a serial chain of particles in each of a few
+// waves; the groups shorten the chain without more partial tiles to fold.  A build of its
+// own, as the group's index costs the large pushes' kernel registers that it has not got.
+template <typename InT, int PREC, int W, int DPW, int V, bool KSPLIT>
+__device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, int64_t p_begin,
+                                                 int64_t p_end, int chunk, int groups,
+                                                 float4* __restrict__ out, int row, float4* smem4)
 {
     constexpr int P = kChunk;
     constexpr int SUBS = 64 / DPW;
@@ -62,10 +68,11 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
 
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
-    const int waves = nt >> 6;
+    const int waves = KSPLIT ? (nt >> 6) / groups : nt >> 6;   // waves that cover the tile
     const int TO = waves * SUBS * W;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int group = KSPLIT ? __builtin_amdgcn_readfirstlane(tid >> 6) / waves : 0;
+    const int wave = (tid >> 6) - group * waves;
     const int dl = lane % DPW;
     const int ob = wave * SUBS + lane / DPW;
 
@@ -115,7 +122,8 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
         s1r[k] = 0.f; s1i[k] = 0.f; s2r[k] = 0.f; s2i[k] = 0.f;
     }
 
-    for (int64_t c = c_begin; c < c_end; ++c) {
+    for (int64_t p0 = p_begin; p0 < p_end; p0 += chunk) {
+        const int cnt = p_end - p0 < chunk ? (int)(p_end - p0) : chunk;
         // Stages 1-3 gate the workgroup's barriers: their waves get issue priority over the
         // hot loops of other workgroups on the CU (measured +2 %).  The hot loop itself runs
         // one level above the default.
@@ -127,12 +135,10 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
         int tc = threadIdx.x;
         asm volatile("" : "+v"(tc));
         // 1. stage the chunk (SoA, coalesced), widened to FP64, plus the step time.
-        if (tc < P) {
-            const int64_t i = j.i_begin + c * P + tc;
-            const bool ok = i < j.i_end;
-            const int64_t ii = ok ? i : j.i_begin;
+        if (tc < cnt) {
+            const int64_t ii = p0 + tc;
 #pragma unroll
-            for (int f = 0; f < 10; ++f) raw[f * P + tc] = ok ? load_wide<InT>(j.f[f], ii) : 0.0;
+            for (int f = 0; f < 10; ++f) raw[f * P + tc] = load_wide<InT>(j.f[f], ii);
             // step = ii / n_per_step without a 64-bit integer division: the FP64 quotient of
             // two integers below 2^53 is within one of the true one; correct it exactly.
             int64_t step = 0;
@@ -141,13 +147,13 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
                 if (step * j.n_per_step > ii) --step;
                 else if ((step + 1) * j.n_per_step <= ii) ++step;
             }
-            raw[10 * P + tc] = ok ? j.t0 + (double)step * j.dt : 0.0;
-            const float N = ok ? (float)raw[9 * P + tc] : 0.f;
+            raw[10 * P + tc] = j.t0 + (double)step * j.dt;
+            const float N = (float)raw[9 * P + tc];
             nw[tc] = make_float2(N, N * N);
         }
         __syncthreads();
         // 2. per (particle, direction) geometry.
-        for (int i = tc; i < P * TD; i += nt) {
+        for (int i = tc; i < cnt * TD; i += nt) {
             const int m = i / TD;
             int dg = td * TD + (i % TD);
             dg = dg < j.n_dir ? dg : j.n_dir - 1;
@@ -158,17 +164,20 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
             taus[i] = ph;
         }
         // 3. per (particle, frequency) form-factor weight F = sqrt(N^2 g + N (1 - g)) (Eq. 12),
-        //    FP32; frequencies outside the grid get F = 0 and contribute nothing.
-        for (int o = tc; o < (SHAPE3 ? 0 : TO); o += nt) {
+        //    FP32; frequencies outside the grid get F = 0 and contribute nothing.  With groups
+        //    there are several threads for each frequency, which take the particles in turn.
+        const int f_step = KSPLIT ? (nt > TO ? nt / TO : 1) : 1;
+        const int f_first = KSPLIT && f_step > 1 ? tc / TO : 0;
+        for (int o = tc - f_first * TO; o < (SHAPE3 || f_first >= f_step ? 0 : TO); o += nt) {
             const int og = tw * TO + o;
             float2 g = make_float2(0.f, 0.f);
             if (og < j.n_omega) {
                 const float* gt = reinterpret_cast<const float*>(j.gtab);
                 g = make_float2(gload(gt, 2 * (int64_t)og), gload(gt, 2 * (int64_t)og + 1));
             }
-            float* dst = ff + o;
+            float* dst = ff + o + f_first * TO;
 #pragma unroll 8
-            for (int m = 0; m < P; ++m, dst += TO) {
+            for (int m = f_first; m < cnt; m += f_step, dst += f_step * TO) {
                 const float2 N = nw[m];
                 const float Fo = __builtin_amdgcn_sqrtf(fmaf(N.y, g.x, N.x * g.y));
                 *dst = (TT && (o & 2)) ? -Fo : Fo;   // sigma_k of the three-term walk
@@ -177,7 +186,7 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
         __syncthreads();
         __builtin_amdgcn_s_setprio(1);
         // 4. hot loop.
-        for (int m = 0; m < P; ++m) {
+        for (int m = group; m < cnt; m += KSPLIT ? groups : 1) {
             const float4 gm = geo[m * TD + dl];
             const double ph = taus[m * TD + dl];
             float zr = 1.f, zi = 0.f;
@@ -360,8 +369,27 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
     int te = threadIdx.x;
     asm volatile("" : "+v"(te));
     const int dl_e = (te & 63) % DPW;
-    const int o_loc = ((te >> 6) * SUBS + (te & 63) / DPW) * W;
-    if (td * TD + dl_e < j.n_dir) {
+    const int o_loc = (((te >> 6) - group * waves) * SUBS + (te & 63) / DPW) * W;
+    if constexpr (KSPLIT) {
+        // the groups' sums: the upper half of them hands its accumulators to the lower half
+        for (int half = groups >> 1; half > 0; half >>= 1) {
+            float4* slot = smem4 + ((te >> 6) - (group >= half ? half * waves : 0)) * W * 64 + (te & 63);
+            if (group >= half && group < 2 * half) {
+#pragma unroll
+                for (int k = 0; k < W; ++k) slot[k * 64] = make_float4(s1r[k], s1i[k], s2r[k], s2i[k]);
+            }
+            __syncthreads();
+            if (group < half) {
+#pragma unroll
+                for (int k = 0; k < W; ++k) {
+                    const float4 v = slot[k * 64];
+                    s1r[k] += v.x; s1i[k] += v.y; s2r[k] += v.z; s2i[k] += v.w;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (group == 0 && td * TD + dl_e < j.n_dir) {
 #pragma unroll
         for (int k = 0; k < W; ++k) {
             if (tw * TO + o_loc + k < j.n_omega)
@@ -399,12 +427,12 @@ constexpr int min_waves(int W, int V)
     return W == 32 ? RAD_W32_WAVES : ((V == 0 || V == kVarBlockStep) ? RAD_W16_WAVES : RAD_W16V_WAVES);
 }
 
-template <typename InT, int PREC, int W, int DPW, int V>
+template <typename InT, int PREC, int W, int DPW, int V, bool KSPLIT>
 __global__ void __launch_bounds__(512, min_waves(W, V)) k_accumulate(AccArgs a)
 {
     extern __shared__ float4 smem4[];
     constexpr int TD = DPW;
-    const int TO = (blockDim.x >> 6) * (64 / DPW) * W;
+    const int TO = (KSPLIT ? (blockDim.x >> 6) / a.ksplit : blockDim.x >> 6) * (64 / DPW) * W;
     const int ntiles = a.job.tiles_d * a.job.tiles_w;
     // Workgroups are handed to the 8 XCDs round-robin; renumber them so that consecutive
     // virtual ids -- the tiles of one particle split, which read the same particle chunk --
@@ -414,15 +442,13 @@ __global__ void __launch_bounds__(512, min_waves(W, V)) k_accumulate(AccArgs a)
     const int split = v / ntiles;
     const int td = tile % a.job.tiles_d;
     const int tw = tile / a.job.tiles_d;
-    const int64_t n_local = a.job.i_end - a.job.i_begin;
-    const int64_t nchunks = (n_local + kChunk - 1) / kChunk;
-    const int64_t c_begin = (int64_t)split * a.chunks_per_split;
-    int64_t c_end = c_begin + a.chunks_per_split;
-    if (c_end > nchunks) c_end = nchunks;
+    const int64_t p_begin = a.job.i_begin + (int64_t)split * a.per_split;
+    const int64_t p_end = p_begin + a.per_split < a.job.i_end ? p_begin + a.per_split : a.job.i_end;
     // partial layout [split][omega][dir]
     float4* out = reinterpret_cast<float4*>(a.part) +
                   ((int64_t)split * a.job.n_omega + (int64_t)tw * TO) * a.job.n_dir + td * TD;
-    accumulate_range<InT, PREC, W, DPW, V>(a.job, td, tw, c_begin, c_end, out, a.job.n_dir, smem4);
+    accumulate_range<InT, PREC, W, DPW, V, KSPLIT>(a.job, td, tw, p_begin, p_end, a.chunk, a.ksplit, out, a.job.n_dir,
+                                                   smem4);
 }
 
 // Persistent batched accumulate: block r processes segments [wg_seg_begin[r], wg_seg_begin[r+1]),
@@ -444,7 +470,9 @@ __global__ void __launch_bounds__(512, min_waves(W, V)) k_accumulate_batch(const
         const int td = sg.tile % j.tiles_d;
         const int tw = sg.tile / j.tiles_d;
         float4* out = reinterpret_cast<float4*>(seg_part) + (int64_t)s * TO * TD;
-        accumulate_range<InT, PREC, W, DPW, V>(j, td, tw, sg.c_begin, sg.c_end, out, TD, smem4);
+        const int64_t p_begin = j.i_begin + sg.c_begin * kChunk, p_cut = j.i_begin + sg.c_end * kChunk;
+        accumulate_range<InT, PREC, W, DPW, V, false>(j, td, tw, p_begin, p_cut < j.i_end ? p_cut : j.i_end, kChunk, 1,
+                                                      out, TD, smem4);
     }
 }
 
@@ -473,18 +501,21 @@ template <typename InT, int PREC, int W, int DPW, int V>
 hipError_t launch_acc_t(const AccArgs& a, const LaunchShape& s, int n_blocks, hipStream_t st,
                         hipEvent_t ev_start, hipEvent_t ev_stop)
 {
-    auto kern = k_accumulate<InT, PREC, W, DPW, V>;
-    const size_t lds = acc_lds_bytes(s);
-    static std::atomic<size_t> lds_allowed[kMaxDevices] = {};   // per instantiation and device
-    const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed);
+    auto kern = a.ksplit > 1 ? k_accumulate<InT, PREC, W, DPW, V, true> : k_accumulate<InT, PREC, W, DPW, V, false>;
+    // the chunk's arrays, then (ksplit > 1) the accumulators of half the groups
+    const size_t half = (size_t)(a.ksplit / 2) * s.waves * 64 * s.w_per_lane * sizeof(float4);
+    const size_t lds = std::max(acc_lds_bytes(s), half);
+    const int threads = 64 * s.waves * a.ksplit;
+    static std::atomic<size_t> lds_allowed[2][kMaxDevices] = {};   // per instantiation and device
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed[a.ksplit > 1]);
     if (e != hipSuccess) return e;
     if (ev_start || ev_stop) {
         AccArgs arg = a;
         void* args[] = {&arg};
-        return hipExtLaunchKernel(reinterpret_cast<const void*>(kern), dim3(n_blocks), dim3(64 * s.waves), args, lds,
+        return hipExtLaunchKernel(reinterpret_cast<const void*>(kern), dim3(n_blocks), dim3(threads), args, lds,
                                   st, ev_start, ev_stop, 0);
     }
-    hipLaunchKernelGGL(kern, dim3(n_blocks), dim3(64 * s.waves), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(n_blocks), dim3(threads), lds, st, a);
     return hipGetLastError();
 }
 

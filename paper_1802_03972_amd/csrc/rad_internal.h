@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+struct rad_batcher;
+
 namespace rad {
 
 // Particles staged per workgroup chunk (one LDS round).
@@ -40,12 +42,14 @@ constexpr int kVarBlockStep = 4;  // piecewise-uniform list: frequency walk with
 constexpr int kBlockW = 16;
 
 // Arguments of the per-grid accumulate kernel: block b handles tile b % ntiles of split
-// b / ntiles, i.e. chunks [split * chunks_per_split, +chunks_per_split) of the job.
+// b / ntiles, i.e. particles [split * per_split, +per_split) of the job, `chunk` at a time.
 struct AccArgs {
     Job job;
     float* part;            // [splits][n_omega][n_dir][4] per-workgroup partial sums
     int32_t splits;
-    int64_t chunks_per_split;
+    int64_t per_split;
+    int32_t chunk;          // at most kChunk
+    int32_t ksplit;         // groups of waves that share a chunk's particles (1, 2, 4, 8)
 };
 
 // Batched launch: every workgroup walks its own list of segments; a segment is a chunk
@@ -94,6 +98,9 @@ inline size_t acc_lds_bytes(const LaunchShape& s)
     const size_t td = tile_dirs(s), to = tile_omegas(s);
     return kChunk * td * 16 + kChunk * td * 8 + 11 * kChunk * 8 + kChunk * 8 + kChunk * to * 4;
 }
+
+// Limits the FP32 sums of a batcher's segments to `chunks` chunks of kChunk particles.
+void batcher_limit_segments(rad_batcher* b, int64_t chunks);
 
 // Sets the calling thread's message returned by rad_last_error().
 void set_last_error(const char* msg);

@@ -274,6 +274,8 @@ namespace {
 // Particles handled per workgroup in one launch at most (bounds the FP32 partial sums;
 // longer pushes are cut into several launches, each folded into the FP64 accumulator).
 constexpr int64_t kMaxPerWorkgroup = 32768;
+constexpr int64_t kMinPerSplit = 8;
+constexpr int kMaxWaves = 8;     // of one workgroup
 
 LaunchShape shape_of(const rad_tile& t, int variant = 0)
 {
@@ -428,23 +430,37 @@ void fill_job(rad::Job& j, const rad_grid* g, const rad_particles* p, double t0,
     j.err = g->d_err;
 }
 
-// Cuts particles [0, total) into launches of at most target_splits particle splits of at
-// most kMaxPerWorkgroup particles each, and sets a's particle range, split count and
-// chunks per split for each launch before calling fn() (which returns a status code).
+// Cuts particles [0, total) into launches of at most target_splits particle splits of at most
+// kMaxPerWorkgroup particles each, and sets a's particle range and its split into workgroups
+// for each launch before calling fn() (which returns a status code).  `waves` is the waves of
+// a workgroup that covers the tile once.
+//
+// From target_splits full chunks on there is one split for each workgroup that the tile asks
+// for, all of the same length to one particle, in chunks of one length.  A smaller push has
+// fewer chunks than that: the idle waves first share the chunks' particles (ksplit, up to
+// eight waves a workgroup), then the splits get shorter, down to kMinPerSplit particles.
 template <typename Fn>
-int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, Fn fn)
+int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, int waves, Fn fn)
 {
     const int64_t per_launch_cap = target_splits * kMaxPerWorkgroup;
     for (int64_t i0 = 0; i0 < total; i0 += per_launch_cap) {
         const int64_t i1 = std::min(total, i0 + per_launch_cap);
-        const int64_t nchunks = (i1 - i0 + rad::kChunk - 1) / rad::kChunk;
-        int64_t splits = std::min<int64_t>(target_splits, nchunks);
-        const int64_t cps = (nchunks + splits - 1) / splits;
-        splits = (nchunks + cps - 1) / cps;
+        const int64_t n = i1 - i0;
+        int64_t per = (n + target_splits - 1) / target_splits;
+        int ksplit = 1;
+        if (per <= rad::kChunk) {
+            per = rad::kChunk;
+            auto fits = [&](int64_t p, int k) { return (n + p - 1) / p * k <= target_splits; };
+            while (2 * ksplit * waves <= kMaxWaves && fits(per, 2 * ksplit)) ksplit *= 2;
+            while (per > kMinPerSplit && fits(per / 2, ksplit)) per /= 2;
+        }
+        const int64_t chunks = (per + rad::kChunk - 1) / rad::kChunk;
         a.job.i_begin = i0;
         a.job.i_end = i1;
-        a.splits = (int32_t)splits;
-        a.chunks_per_split = cps;
+        a.splits = (int32_t)((n + per - 1) / per);
+        a.per_split = per;
+        a.chunk = (int32_t)((per + chunks - 1) / chunks);
+        a.ksplit = ksplit;
         if (int rc = fn()) return rc;
     }
     return RAD_OK;
@@ -490,7 +506,7 @@ int push_range(rad_grid* g, double t0, int64_t n_per_step, int64_t total, const 
     const int64_t target_splits = max_splits(g);   // <= part_splits (capacity may be larger)
     AccArgs a{};
     fill_job(a.job, g, p, t0, n_per_step, g->tile);
-    return for_each_launch(a, total, target_splits, [&]() -> int {
+    return for_each_launch(a, total, target_splits, ls.waves, [&]() -> int {
         const int64_t i0 = a.job.i_begin, i1 = a.job.i_end, splits = a.splits;
         const int b = g->part_next;
         g->part_next ^= 1;
@@ -851,7 +867,7 @@ int rad_push_step_noalloc(rad_grid* g, double t, int64_t n_particles, const rad_
     AccArgs a{};
     fill_job(a.job, g, p, t, n_particles, g->tile);
     a.part = scr;
-    rc = for_each_launch(a, n_particles, std::min<int64_t>(max_splits(g), cap_splits), [&]() -> int {
+    rc = for_each_launch(a, n_particles, std::min<int64_t>(max_splits(g), cap_splits), ls.waves, [&]() -> int {
         // same stream: a launch's accumulate rewrites the scratch only after the previous
         // launch's fold has read it
         hipError_t e = rad::launch_accumulate(a, p->dtype, g->precision, ls, (int)(a.splits * nt), st);
@@ -1051,6 +1067,9 @@ struct rad_batcher {
     // graph mode: captured [plan upload -> accumulate -> fold] per launch configuration
     bool tile_set = false;       // launch shape of the batched kernel (else the built-in
     rad_tile tile{};             // heuristic for the first item's grid shape)
+    // A segment sums at most this many chunks in FP32 (the range's end and the tile's are the
+    // other limits).  The server sets it.
+    int64_t seg_chunks = INT64_MAX;
     bool graph_mode = false;
     hipStream_t cap_stream = nullptr;
     std::vector<BatchGraph> graphs;
@@ -1116,14 +1135,9 @@ struct LaunchPlan {
     std::vector<int32_t> seg_list;
 };
 
-// A segment sums at most this many chunks (512 particles) in FP32: the rounding of such a sum
-// grows with its length (about as its square root), and a bunch that fits in one range would
-// otherwise be one sum of a few thousand particles.  More segments cost partial tiles: twelve
-// uneven bunches write 2.2 times as many as with one segment per tile of a range, at the same
-// time per push, and their worst error against FP64 falls from 1.8e-6 to 1.1e-6.
-constexpr int64_t kMaxSegChunks = 16;
-// Segments a workgroup may have in graph mode, whose buffers have a fixed size (longer
-// launches get longer segments there).
+// Segments a workgroup may have in graph mode, whose buffers have a fixed size: one for each
+// tile it meets, or, with a limit on their length, this many on average (longer launches get
+// longer segments then).
 constexpr int kGraphSegsPerRange = 8;
 
 void build_plan(const std::vector<ItemInfo>& items, int64_t L0, int64_t L1, int R, int64_t max_seg, LaunchPlan& pl)
@@ -1142,7 +1156,7 @@ void build_plan(const std::vector<ItemInfo>& items, int64_t L0, int64_t L1, int 
             const int64_t local = pos - in.iter_begin;
             const int64_t tile = local / in.chunks;
             const int64_t c0 = local % in.chunks;
-            const int64_t seg_end = std::min(std::min(end, in.iter_begin + (tile + 1) * in.chunks), pos + max_seg);
+            const int64_t seg_end = std::min(pos + std::min(end - pos, max_seg), in.iter_begin + (tile + 1) * in.chunks);
             pl.segs.push_back(rad::BatchSeg{(int32_t)it, (int32_t)tile, c0, c0 + (seg_end - pos)});
             pos = seg_end;
         }
@@ -1215,6 +1229,8 @@ extern "C" int rad_batcher_destroy(rad_batcher* b)
     free_batcher(b);
     return RAD_OK;
 }
+
+void rad::batcher_limit_segments(rad_batcher* b, int64_t chunks) { b->seg_chunks = chunks; }
 
 extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int32_t n_items, void* stream)
 {
@@ -1292,8 +1308,8 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
     for (int64_t L0 = 0; L0 < I; L0 += per_launch) {
         const int64_t L1 = std::min(I, L0 + per_launch);
         const int R = (int)std::min<int64_t>(R_target, L1 - L0);
-        int64_t max_seg = kMaxSegChunks;
-        if (b->graph_mode) {
+        int64_t max_seg = b->seg_chunks;
+        if (b->graph_mode && max_seg < INT64_MAX) {
             const int64_t most = (int64_t)R_target * (kGraphSegsPerRange - 1);
             max_seg = std::max(max_seg, (L1 - L0 + most - 1) / most);
         }
@@ -1304,7 +1320,8 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
         // so one captured graph serves every plan that fits.
         const int R_fixed = R_target;
         const size_t jobs_cap_g = (size_t)R_fixed + 16 * (size_t)b->max_items;
-        const size_t segs_cap_g = (size_t)kGraphSegsPerRange * R_fixed + 16 * (size_t)b->max_items;
+        const size_t segs_cap_g = (b->seg_chunks < INT64_MAX ? (size_t)kGraphSegsPerRange * R_fixed : (size_t)R_fixed) +
+                                   16 * (size_t)b->max_items;
         bool use_graph = b->graph_mode && pl.segs.size() <= segs_cap_g && pl.jobs.size() <= jobs_cap_g &&
                          pl.seg_list.size() <= segs_cap_g;
         const int R_launch = use_graph ? R_fixed : R;
