@@ -439,6 +439,9 @@ void fill_job(rad::Job& j, const rad_grid* g, const rad_particles* p, double t0,
 // for, all of the same length to one particle, in chunks of one length.  A smaller push has
 // fewer chunks than that: the idle waves first share the chunks' particles (ksplit, up to
 // eight waves a workgroup), then the splits get shorter, down to kMinPerSplit particles.
+// 1024 particles x 16 x 64 points 19.0 -> 8.2 us (128 workgroups of 8 waves instead of 32 of
+// one), 2000 x 2 x 241 of an explicit list 22.6 -> 10.7; 50000 x 128 x 256 of a block-stepped
+// list, 391 particles a split instead of 13 chunks in 121 of 128 splits, 380 -> 355.
 template <typename Fn>
 int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, int waves, Fn fn)
 {
