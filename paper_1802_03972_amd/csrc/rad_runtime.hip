@@ -291,27 +291,58 @@ int tiles_w(const rad_grid* g)
 int max_splits(const rad_grid* g)
 {
     const int nt = tiles_d(g) * tiles_w(g);
-    const int target = g->cus * g->tile.wg_per_cu;
-    return std::max(1, (target + nt - 1) / nt);
+    // rounded down: one split more than fits would run alone, after all the others
+    return std::max(1, g->cus * g->tile.wg_per_cu / nt);
 }
 
+// Launch shape without a measured entry: the tile with the least time per particle over the
+// whole grid, from the cycles that a particle costs its workgroup and the waves that share a
+// SIMD.  What it weighs: lanes outside the grid (an odd number of directions or frequencies
+// fills some tiles badly: 40 x 600 points are 48 x 1024 in 16-direction tiles of 8 waves, 48 x
+// 640 in tiles of 5), the set-up that a tile's frequencies and directions share, and the
+// workgroups that registers and LDS let run together.  Against 32 directions up to 256
+// frequencies, else 16, and as many waves as the frequencies fill (push with fold, one card):
+// 30000 x 37 x 100 76 -> 68 us, x 40 x 600 391 -> 245, 20000 x 88 x 730 527 -> 313, 30000 x 88 x
+// 200 of an explicit list 451 -> 277, cubic cells 415 -> 259; the best of all tiles measured 60,
+// 233, 302, 270 and 258.
 rad_tile default_tile(int n_dir, int n_omega, int variant = 0)
 {
-    (void)variant;
-    rad_tile t{};
-    // 16 frequencies per lane (the four-waves-per-SIMD kernels); 32 directions per wave
-    // where the grid has them and the frequencies are few, else 16.  Measured winners on
-    // MI355X: 128 x 256 and 64 x 256 -> 32 x 8 waves, 128 x 512 and 64 x 1024 -> 16 x 8.
-    t.w_per_lane = 16;
-    t.dir_per_wave = (n_dir >= 32 && n_omega <= 256) ? 32 : 16;
-    const int per_wave = (64 / t.dir_per_wave) * t.w_per_lane;
-    t.waves = std::min(8, std::max(1, (n_omega + per_wave - 1) / per_wave));
-    // 16 waves per CU fit (128 VGPRs); LDS also bounds the count.
-    const size_t lds = rad::acc_lds_bytes(shape_of(t));
-    const int by_waves = std::max(1, 16 / t.waves);
-    const int by_lds = std::max(1, (int)((160 * 1024) / lds));
-    t.wg_per_cu = std::max(2, std::min(by_waves, by_lds));
-    return t;
+    // Waves per SIMD by registers (128 VGPRs for the walk kernels; 142 to 175 for the others),
+    // and the cycles of 16 frequencies of one particle in the hot loop.
+    const bool walk = variant == 0 || variant == rad::kVarBlockStep;
+    const int slots = 4 * (walk ? 4 : 3);
+    const double hot = walk ? 480.0 : 830.0;
+    rad_tile best{};
+    double best_cost = 0.0;
+    for (int dpw : {32, 16, 64}) {
+        for (int waves = 8; waves >= 1; --waves) {
+            rad_tile t{};
+            t.w_per_lane = 16;
+            t.dir_per_wave = dpw;
+            t.waves = waves;
+            const int to = rad::tile_omegas(shape_of(t)), per_wave = to / waves;
+            if (waves > 1 && to - per_wave >= n_omega) continue;   // a wave without a frequency
+            const int resident = std::min(slots / waves, (int)((160 * 1024) / rad::acc_lds_bytes(shape_of(t))));
+            if (resident < 1) continue;
+            // one round of resident workgroups; two for the other kernels, whose rounds end
+            // less evenly (88 x 200 explicit list 295 us with one, 277 with two; cubic cells 286
+            // and 259)
+            t.wg_per_cu = std::min(walk ? resident : 2 * resident, 16);
+            // issue rate by waves per SIMD (VOP2 loops: 6.2, 3.3 and 3.0 cycles an instruction at
+            // one, two and four)
+            const double per_simd = resident * waves / 4.0;
+            const double rate = per_simd <= 1.0 ? 0.5 * per_simd
+                                : per_simd <= 2.0 ? 0.5 + 0.38 * (per_simd - 1.0) : 0.88 + 0.06 * (per_simd - 2.0);
+            const double tiles = (double)((n_dir + dpw - 1) / dpw) * ((n_omega + to - 1) / to);
+            // geometry 600 cycles per 64 (particle, direction), weights 25 per 64 (particle, frequency)
+            const double cost = tiles * (waves * hot + dpw * 9.4 + to * 0.4) / rate;
+            if (best_cost == 0.0 || cost < best_cost) {
+                best_cost = cost;
+                best = t;
+            }
+        }
+    }
+    return best;
 }
 
 int validate_tile(const rad_tile& t)

@@ -61,3 +61,14 @@ def test_variants(rad, shape, kind, dtype):
     n_omega = 75
     om = {"uniform": None, "log": np.geomspace(1e15, 1e19, n_omega), "blocks": block_log_omegas(1e15, 1e19, n_omega)}
     check(rad, 150, 3, 5, n_omega, shape=shape, dtype=dtype, omegas=om[kind], steps=3)
+
+
+# grids that fill their tiles badly: the default launch shape's choices of directions per wave,
+# of waves (one to eight, odd numbers too) and of frequency tiles
+@pytest.mark.parametrize("nx,ny,n_omega,shape,kind", [
+    (37, 1, 100, "cic", "uniform"), (8, 5, 600, "cic", "uniform"), (8, 16, 100, "tsc", "uniform"),
+    (8, 3, 200, "gauss", "uniform"), (8, 11, 137, "cic3d", "uniform"), (8, 11, 137, "cic", "log"),
+    (1, 1, 1000, "cic", "uniform"), (8, 16, 17, "cic", "blocks"), (1, 1, 1, "cic", "uniform")])
+def test_default_launch_shapes(rad, nx, ny, n_omega, shape, kind):
+    om = {"uniform": None, "log": np.geomspace(1e15, 1e19, n_omega), "blocks": block_log_omegas(1e15, 1e19, n_omega)}
+    check(rad, 1200, nx, ny, n_omega, shape=shape, omegas=om[kind])
