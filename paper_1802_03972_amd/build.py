@@ -13,7 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "librad.so")
-SOURCES = ["rad_accumulate.hip", "rad_kernels.hip", "rad_runtime.hip", "rad_server.hip"]
+SOURCES = ["rad_accumulate.hip", "rad_matrix.hip", "rad_kernels.hip", "rad_runtime.hip", "rad_server.hip"]
 # the files that define the accumulate kernels (profiles taken on them are keyed to their hash)
 ACCUMULATE_FILES = ["rad_internal.h", "rad_device.h", "rad_accumulate.hip"]
 ARCH = os.environ.get("RAD_OFFLOAD_ARCH", "gfx950")

@@ -139,15 +139,7 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
             const int64_t ii = p0 + tc;
 #pragma unroll
             for (int f = 0; f < 10; ++f) raw[f * P + tc] = load_wide<InT>(j.f[f], ii);
-            // step = ii / n_per_step without a 64-bit integer division: the FP64 quotient of
-            // two integers below 2^53 is within one of the true one; correct it exactly.
-            int64_t step = 0;
-            if (j.i_end > j.n_per_step) {
-                step = (int64_t)floor((double)ii / (double)j.n_per_step);
-                if (step * j.n_per_step > ii) --step;
-                else if ((step + 1) * j.n_per_step <= ii) ++step;
-            }
-            raw[10 * P + tc] = j.t0 + (double)step * j.dt;
+            raw[10 * P + tc] = step_time(j, ii);
             const float N = (float)raw[9 * P + tc];
             nw[tc] = make_float2(N, N * N);
         }

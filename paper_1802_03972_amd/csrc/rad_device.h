@@ -74,18 +74,28 @@ __device__ __forceinline__ double load_wide(const void* p, int64_t i)
     return static_cast<double>(gload(static_cast<const InT*>(p), i));
 }
 
+// Time of particle i of a job: t0 + step dt with step = i / n_per_step, without a 64-bit integer
+// division: the FP64 quotient of two integers below 2^53 is within one of the true one and is
+// corrected exactly.
+__device__ __forceinline__ double step_time(const Job& j, int64_t i)
+{
+    int64_t step = 0;
+    if (j.i_end > j.n_per_step) {
+        step = (int64_t)floor((double)i / (double)j.n_per_step);
+        if (step * j.n_per_step > i) --step;
+        else if ((step + 1) * j.n_per_step <= i) ++step;
+    }
+    return j.t0 + (double)step * j.dt;
+}
+
 // Per (particle, direction) geometry.  Writes A1, A2 (FP32), w = exp(i domega tau) and
 // tau/(2 pi) (FP64).
-template <int PREC, bool WANT_W, int P = kChunk>
-__device__ __forceinline__ void particle_direction_setup(const double* __restrict__ raw, int m,
-                                                         const double* __restrict__ dv,
-                                                         double domega, float4& geo,
-                                                         double& ph_out, int* err)
+template <int PREC, bool WANT_W>
+__device__ __forceinline__ void particle_direction_geometry(double x, double y, double z, double bx, double by,
+                                                            double bz, double dbx, double dby, double dbz, double N,
+                                                            double t, const double* __restrict__ dv, double domega,
+                                                            float4& geo, double& ph_out, int* err)
 {
-    const double x = raw[0 * P + m], y = raw[1 * P + m], z = raw[2 * P + m];
-    const double bx = raw[3 * P + m], by = raw[4 * P + m], bz = raw[5 * P + m];
-    const double dbx = raw[6 * P + m], dby = raw[7 * P + m], dbz = raw[8 * P + m];
-    const double N = raw[9 * P + m], t = raw[10 * P + m];
     const double nx = gload(dv, 0), ny = gload(dv, 1), nz = gload(dv, 2);
     const double e1x = gload(dv, 3), e1y = gload(dv, 4), e1z = gload(dv, 5);
     const double e2x = gload(dv, 6), e2y = gload(dv, 7), e2z = gload(dv, 8);
@@ -148,6 +158,18 @@ __device__ __forceinline__ void particle_direction_setup(const double* __restric
     if (bad) flag_error(err);
     geo = make_float4(A1, A2, wr, wi);
     ph_out = ph;
+}
+
+// The same for particle m of a chunk staged in LDS (field-major, P particles a field).
+template <int PREC, bool WANT_W, int P = kChunk>
+__device__ __forceinline__ void particle_direction_setup(const double* __restrict__ raw, int m,
+                                                         const double* __restrict__ dv, double domega, float4& geo,
+                                                         double& ph_out, int* err)
+{
+    particle_direction_geometry<PREC, WANT_W>(raw[0 * P + m], raw[1 * P + m], raw[2 * P + m], raw[3 * P + m],
+                                              raw[4 * P + m], raw[5 * P + m], raw[6 * P + m], raw[7 * P + m],
+                                              raw[8 * P + m], raw[9 * P + m], raw[10 * P + m], dv, domega, geo, ph_out,
+                                              err);
 }
 
 }  // namespace

@@ -52,6 +52,20 @@ struct AccArgs {
     int32_t ksplit;         // groups of waves that share a chunk's particles (1, 2, 4, 8)
 };
 
+// Arguments of the matrix-core accumulate kernel: frequencies [k0, k0 + n_sub) of the job's grid,
+// all with the shape factor g (g1 = 1 - g), in fgroups groups of rg x 256; one wave for each
+// (particle split, frequency group, direction).
+struct MxArgs {
+    Job job;
+    float* part;            // [splits][n_sub][n_dir][4]
+    float g, g1;
+    int32_t k0, n_sub;
+    int32_t fgroups;
+    int32_t splits;
+    int64_t per_split;
+};
+constexpr int kMxBlock = 256;   // frequencies of a row group
+
 // Batched launch: every workgroup walks its own list of segments; a segment is a chunk
 // range of one (item, tile) and owns one partial tile [TO][TD][4] in the segment buffer.
 struct BatchSeg {
@@ -111,6 +125,10 @@ void set_last_error(const char* msg);
 hipError_t launch_accumulate(const AccArgs& a, int dtype, int precision, const LaunchShape& s,
                              int n_blocks, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr);
+hipError_t launch_accumulate_mx(const MxArgs& a, int dtype, int rg, hipStream_t st, hipEvent_t ev_start = nullptr,
+                                hipEvent_t ev_stop = nullptr);
+// Waves of the matrix-core kernel with rg row groups (1..4) that one CU holds.
+int mx_resident_waves(int rg);
 // count = 4 * grid points (FP32 values per split); part is 16-byte aligned.
 hipError_t launch_fold(const float* part, double* S, int splits, int64_t count, hipStream_t st,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);

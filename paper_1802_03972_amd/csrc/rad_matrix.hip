@@ -1,0 +1,259 @@
+// Matrix-core accumulate kernel for the frequencies of a uniform grid over which the 1-D shape
+// factor g is one constant (a point shape everywhere; a Gaussian wherever it has underflowed
+// to zero, which is all but the first few frequencies of a wide grid).
+//
+// There the weight F_m of a macro-particle does not depend on the frequency, so with
+// omega_k = Omega_q + j domega (k = 16 q + j) the sum over particles
+//     S(n, k) = sum_m [F_m A_m(n) exp(i j domega tau_m)] exp(i Omega_q tau_m)
+// is, for each direction, a matrix product over the particles: rows (q, re/im), columns
+// (j, re/im) for each of the two polarizations.  The general kernel spends 8 VALU operations on
+// each term; here a term's 8 multiply-adds are the matrix cores', and the VALU only forms the
+// factors: 32 row and 64 column values per particle for 256 frequencies.
+//
+// * Factors.  Each is sin or cos of an FP64 phase, reduced to [0, 1) revolutions before it
+//   leaves FP64 (cos as sin a quarter revolution on); nothing is walked.  The columns carry
+//   F A in FP32.
+// * FP32 product on bf16 matrix cores.  Each FP32 factor is split into three bf16 parts whose
+//   sum it is (8 + 8 + 8 bits, the exponent range of FP32), and the six products of parts down
+//   to 2^-16 of the largest are accumulated in FP32; the ones left out are below 2^-24.  The FP32
+//   matrix instructions take 16 cycles for 64 terms and add to the VALU's time; the bf16 ones
+//   take 3.75 cycles of it and run beside the rest.
+// * A wave owns one direction and RG x 256 frequencies, and shares nothing with other waves:
+//   64 particles at a time, each lane computes one particle's geometry (FP64, as in the general
+//   kernel) into the wave's own LDS, then four steps of 16 particles.  Consecutive waves take
+//   consecutive directions, so that their 16-byte partial sums fill lines.
+// * Bound by the VALU: per 16 particles about 510 cycles for the columns and 320 for each 256
+//   frequencies' rows, half of it the splits, plus 20 for each of the 12 matrix instructions.
+//   RAD_MX_FIG
+#include <hip/hip_ext.h>
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include "rad_device.h"
+#include "rad_internal.h"
+
+namespace rad {
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kMxThreads = 256;
+constexpr int kMxParts = 3;
+
+// A particle as the matrix loop needs it: tau / (2 pi) and F A in the two polarizations.
+struct __align__(16) MxParticle {
+    double ph;
+    float a1, a2;
+};
+
+// Two FP32 values as three bf16 pairs (packed, first value in the low half) that add up to them.
+__device__ __forceinline__ void split_pair(float v0, float v1, uint32_t (&out)[kMxParts])
+{
+#pragma unroll
+    for (int p = 0; p < kMxParts; ++p) {
+        const f32x2 v = {v0, v1};
+        const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+        out[p] = b;
+        if (p + 1 < kMxParts) {
+            v0 -= __builtin_bit_cast(float, b << 16);
+            v1 -= __builtin_bit_cast(float, b & 0xffff0000u);
+        }
+    }
+}
+
+// sin of 2 pi (om ph + quarter), the phase reduced in FP64.
+__device__ __forceinline__ float phase_sin(double om, double ph, double quarter)
+{
+    return __builtin_amdgcn_sinf(static_cast<float>(frac_rev(fma(om, ph, quarter))));
+}
+
+// Orders this wave's LDS writes before its later reads of other lanes' values.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int mx_waves(int RG) { return RG == 1 ? 4 : RG == 2 ? 3 : 2; }
+
+template <typename InT, int RG>
+__global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxArgs a)
+{
+    __shared__ MxParticle buf_all[kMxThreads];
+    const Job& j = a.job;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    MxParticle* buf = buf_all + 64 * wave;
+    // this wave's direction, frequency group and particle split
+    const int id = (int)blockIdx.x * (kMxThreads / 64) + wave;
+    if (id >= a.splits * a.fgroups * j.n_dir) return;      // no barriers below
+    const int d = id % j.n_dir, fg = id / j.n_dir % a.fgroups, split = id / j.n_dir / a.fgroups;
+    const int64_t p_begin = j.i_begin + (int64_t)split * a.per_split;
+    const int64_t p_end = p_begin + a.per_split < j.i_end ? p_begin + a.per_split : j.i_end;
+
+    const int r = lane & 31, half = lane >> 5;
+    double om_row[RG];
+#pragma unroll
+    for (int g = 0; g < RG; ++g) {
+        const int k = a.k0 + ((fg * RG + g) * 16 + (r >> 1)) * 16;
+        om_row[g] = gload(j.omega, k < j.n_omega ? k : j.n_omega - 1);
+    }
+    const double quarter_row = (r & 1) ? 0.0 : 0.25;        // even rows cos, odd rows sin
+    const double om_col = (double)(r & 15) * j.domega;
+    const double quarter_col = r < 16 ? 0.25 : 0.0;         // columns 0..15 cos, 16..31 sin
+
+    f32x16 acc[RG][2];
+#pragma unroll
+    for (int g = 0; g < RG; ++g) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[g][0][i] = acc[g][1][i] = 0.f;
+    }
+
+    // the next 64 particles' fields are loaded while this 64's products run
+    InT f[10];
+    auto load = [&](int64_t p0) {
+        const int64_t i = p0 + lane < p_end ? p0 + lane : p_end - 1;
+#pragma unroll
+        for (int c = 0; c < 10; ++c) f[c] = gload(static_cast<const InT*>(j.f[c]), i);
+    };
+    if (p_begin < p_end) load(p_begin);
+    for (int64_t p0 = p_begin; p0 < p_end; p0 += 64) {
+        const int cnt = p_end - p0 < 64 ? (int)(p_end - p0) : 64;
+        {
+            const int64_t i = p0 + lane < p_end ? p0 + lane : p_end - 1;
+            const double t = step_time(j, i);
+            float4 geo;
+            double ph;
+            particle_direction_geometry<0, false>((double)f[0], (double)f[1], (double)f[2], (double)f[3], (double)f[4],
+                                                  (double)f[5], (double)f[6], (double)f[7], (double)f[8], (double)f[9],
+                                                  t, j.dirs9 + 9 * d, 0.0, geo, ph, j.err);
+            const float N = (float)f[9];
+            const float F = __builtin_amdgcn_sqrtf(fmaf(N * N, a.g, N * a.g1));
+            const bool ok = lane < cnt;
+            MxParticle e;
+            e.ph = ok ? ph : 0.0;
+            e.a1 = ok ? F * geo.x : 0.f;
+            e.a2 = ok ? F * geo.y : 0.f;
+            wave_lds_sync();                               // the last 64's reads are done
+            buf[lane] = e;
+        }
+        if (p0 + 64 < p_end) load(p0 + 64);
+        wave_lds_sync();
+        for (int s = 0; s < cnt; s += 16) {
+            const MxParticle* e = buf + s + 8 * half;      // this half wave's 8 of 16 particles
+            uint32_t col[2][kMxParts][4];
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) {
+                const MxParticle e0 = e[i], e1 = e[i + 1];
+                const float c0 = phase_sin(om_col, e0.ph, quarter_col), c1 = phase_sin(om_col, e1.ph, quarter_col);
+                uint32_t w[kMxParts];
+                split_pair(e0.a1 * c0, e1.a1 * c1, w);
+#pragma unroll
+                for (int p = 0; p < kMxParts; ++p) col[0][p][i / 2] = w[p];
+                split_pair(e0.a2 * c0, e1.a2 * c1, w);
+#pragma unroll
+                for (int p = 0; p < kMxParts; ++p) col[1][p][i / 2] = w[p];
+            }
+#pragma unroll
+            for (int g = 0; g < RG; ++g) {
+                uint32_t row[kMxParts][4];
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) {
+                    uint32_t w[kMxParts];
+                    split_pair(phase_sin(om_row[g], e[i].ph, quarter_row), phase_sin(om_row[g], e[i + 1].ph, quarter_row), w);
+#pragma unroll
+                    for (int p = 0; p < kMxParts; ++p) row[p][i / 2] = w[p];
+                }
+                // parts (row, column) with 2^-(8 (row + column)) down to 2^-16, smallest first
+#pragma unroll
+                for (int sum = kMxParts - 1; sum >= 0; --sum) {
+#pragma unroll
+                    for (int pr = sum; pr >= 0; --pr) {
+                        const u32x4 rw = {row[pr][0], row[pr][1], row[pr][2], row[pr][3]};
+#pragma unroll
+                        for (int pol = 0; pol < 2; ++pol) {
+                            const uint32_t(&cp)[4] = col[pol][sum - pr];
+                            const u32x4 cw = {cp[0], cp[1], cp[2], cp[3]};
+                            acc[g][pol] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, rw),
+                                                                                  __builtin_bit_cast(bf16x8, cw),
+                                                                                  acc[g][pol], 0, 0, 0);
+                        }
+                    }
+                }
+            }
+        }
+    }
+
+    // Accumulator i of a lane is row 8 (i / 4) + 4 half + i % 4, column r: rows 2q (cos) and
+    // 2q + 1 (sin) are neighbours, and column r ^ 16 is the other of (cos, sin) of the same j.
+    // S_re = [cos cos] - [sin sin], S_im = [cos sin] + [sin cos]: one exchange gives the cos
+    // columns' lanes S_re and the sin columns' S_im, a second one whole points: of each two q
+    // the first to the cos column's lane, the second to the sin column's.
+    const bool is_cos = r < 16;
+    float4* out = reinterpret_cast<float4*>(a.part) + (int64_t)split * a.n_sub * j.n_dir + d;
+#pragma unroll
+    for (int g = 0; g < RG; ++g) {
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+            float sv[2][2];                                // [q, q + 1][polarization]
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                for (int pol = 0; pol < 2; ++pol) {
+                    const float other = __shfl_xor(acc[g][pol][i + 2 * u + 1], 16);
+                    sv[u][pol] = is_cos ? acc[g][pol][i + 2 * u] - other : acc[g][pol][i + 2 * u] + other;
+                }
+            }
+            const float t0 = __shfl_xor(is_cos ? sv[1][0] : sv[0][0], 16);
+            const float t1 = __shfl_xor(is_cos ? sv[1][1] : sv[0][1], 16);
+            const float4 v = is_cos ? make_float4(sv[0][0], t0, sv[0][1], t1) : make_float4(t0, sv[1][0], t1, sv[1][1]);
+            const int q = 4 * (i / 4) + 2 * half + (is_cos ? 0 : 1);
+            const int k = ((fg * RG + g) * 16 + q) * 16 + (r & 15);
+            if (k < a.n_sub) out[(int64_t)k * j.n_dir] = v;
+        }
+    }
+}
+
+template <typename InT>
+hipError_t launch_mx_t(const MxArgs& a, int rg, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    const int64_t waves = (int64_t)a.splits * a.fgroups * a.job.n_dir;
+    constexpr int per = kMxThreads / 64;
+    const dim3 grid((unsigned)((waves + per - 1) / per)), block(kMxThreads);
+    auto go = [&](auto kern) -> hipError_t {
+        if (ev_start || ev_stop) {
+            MxArgs arg = a;
+            void* args[] = {&arg};
+            return hipExtLaunchKernel(reinterpret_cast<const void*>(kern), grid, block, args, 0, st, ev_start, ev_stop, 0);
+        }
+        hipLaunchKernelGGL(kern, grid, block, 0, st, a);
+        return hipGetLastError();
+    };
+    switch (rg) {
+    case 1: return go(k_accumulate_mx<InT, 1>);
+    case 2: return go(k_accumulate_mx<InT, 2>);
+    case 3: return go(k_accumulate_mx<InT, 3>);
+    case 4: return go(k_accumulate_mx<InT, 4>);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+int mx_resident_waves(int rg) { return 4 * mx_waves(rg); }
+
+hipError_t launch_accumulate_mx(const MxArgs& a, int dtype, int rg, hipStream_t st, hipEvent_t ev_start,
+                                hipEvent_t ev_stop)
+{
+    return dtype == 0 ? launch_mx_t<float>(a, rg, st, ev_start, ev_stop)
+                      : launch_mx_t<double>(a, rg, st, ev_start, ev_stop);
+}
+
+}  // namespace rad

@@ -226,6 +226,14 @@ struct DeviceGuard {
 
 }  // namespace
 
+// A range of a grid's frequencies and the kernel that accumulates it.
+struct GridPart {
+    int k0 = 0, n = 0;        // frequencies [k0, k0 + n)
+    bool matrix = false;      // matrix-core kernel (k0 and all below: the general one)
+    rad_tile tile{};          // general kernel's launch shape
+    int rg = 0, fgroups = 0;  // matrix kernel: row groups per wave, frequency groups
+};
+
 struct rad_grid {
     int device = 0;
     int n_dir = 0, n_omega = 0;
@@ -242,7 +250,7 @@ struct rad_grid {
     // accumulate while the fold of the previous push (issued on another stream) still
     // reads the other buffer.
     float* d_part[2] = {nullptr, nullptr};
-    int64_t part_splits = 0;
+    size_t part_bytes = 0;
     int part_next = 0;
     // Ordering of the work on S and on the partial-sum buffers (order_after, mark_done).
     struct Mark {
@@ -259,6 +267,9 @@ struct rad_grid {
     float* d_g3 = nullptr;     // [n_dir][n_omega] for 3-D shapes
     double* d_bstep = nullptr; // per-block spacing of a piecewise-uniform frequency list
     int variant = 0;           // rad::kVarDirect | rad::kVarShape3
+    int const_k0 = 0;          // from this frequency on (a multiple of 16; n_omega: none) the
+    float2 const_g{};          // shape table holds one pair (g, 1 - g)
+    std::vector<GridPart> parts;
     bool counted = false;      // among the users of the read-out buffers
     // kernel timing (rad_profile_*)
     bool profiling = false;
@@ -282,18 +293,20 @@ LaunchShape shape_of(const rad_tile& t, int variant = 0)
     return LaunchShape{t.w_per_lane, t.dir_per_wave, t.waves, variant};
 }
 
-int tiles_d(const rad_grid* g) { return (g->n_dir + g->tile.dir_per_wave - 1) / g->tile.dir_per_wave; }
-int tiles_w(const rad_grid* g)
+int tiles_of(const rad_grid* g, const GridPart& p)
 {
-    const int to = rad::tile_omegas(shape_of(g->tile));
-    return (g->n_omega + to - 1) / to;
+    const int to = rad::tile_omegas(shape_of(p.tile));
+    return (g->n_dir + p.tile.dir_per_wave - 1) / p.tile.dir_per_wave * ((p.n + to - 1) / to);
 }
-int max_splits(const rad_grid* g)
+// Particle splits that run together, rounded down: one more than fits would run alone, after
+// all the others.
+int max_splits(const rad_grid* g, const GridPart& p)
 {
-    const int nt = tiles_d(g) * tiles_w(g);
-    // rounded down: one split more than fits would run alone, after all the others
-    return std::max(1, g->cus * g->tile.wg_per_cu / nt);
+    const int64_t per_split = p.matrix ? (int64_t)g->n_dir * p.fgroups : tiles_of(g, p);
+    const int64_t fit = (int64_t)g->cus * (p.matrix ? rad::mx_resident_waves(p.rg) : p.tile.wg_per_cu);
+    return (int)std::max<int64_t>(1, fit / per_split);
 }
+size_t split_bytes(const rad_grid* g, const GridPart& p) { return (size_t)p.n * g->n_dir * 4 * sizeof(float); }
 
 // Launch shape without a measured entry: the tile with the least time per particle over the
 // whole grid, from the cycles that a particle costs its workgroup and the waves that share a
@@ -305,7 +318,7 @@ int max_splits(const rad_grid* g)
 // 30000 x 37 x 100 76 -> 68 us, x 40 x 600 391 -> 245, 20000 x 88 x 730 527 -> 313, 30000 x 88 x
 // 200 of an explicit list 451 -> 277, cubic cells 415 -> 259; the best of all tiles measured 60,
 // 233, 302, 270 and 258.
-rad_tile default_tile(int n_dir, int n_omega, int variant = 0)
+rad_tile default_tile(int n_dir, int n_omega, int variant = 0, double* cost_out = nullptr)
 {
     // Waves per SIMD by registers (128 VGPRs for the walk kernels; 142 to 175 for the others),
     // and the cycles of 16 frequencies of one particle in the hot loop.
@@ -342,7 +355,50 @@ rad_tile default_tile(int n_dir, int n_omega, int variant = 0)
             }
         }
     }
+    if (cost_out) *cost_out = best_cost;
     return best;
+}
+
+// Row groups per wave and frequency groups of the matrix kernel for n frequencies, and its cost
+// on default_tile's scale: per 16 particles 510 cycles for the columns and 560 for each row
+// group, 450 per 64 particles for the geometry.
+double matrix_shape(int n_dir, int n, int* rg, int* fgroups)
+{
+    const int groups = (n + rad::kMxBlock - 1) / rad::kMxBlock;
+    *fgroups = (groups + 3) / 4;
+    *rg = (groups + *fgroups - 1) / *fgroups;
+    const double rate = *rg == 1 ? 1.0 : *rg == 2 ? 0.94 : 0.88;
+    return (double)n_dir * *fgroups * ((510.0 + 560.0 * *rg) / 16.0 + 7.0) / rate;
+}
+
+// Which kernel accumulates which frequencies.  The matrix kernel takes the frequencies over
+// which the shape factor is one constant (the end of the grid from a multiple of 16 on) where
+// its waves of 256 frequencies of one direction cost less than the general kernel's tiles:
+// from about 150 frequencies on, from fewer for directions that fill a tile badly.  RAD_MX_LINE
+void plan_parts(rad_grid* g)
+{
+    g->parts.clear();
+    const int n_mx = g->n_omega - g->const_k0;
+    if (g->variant == 0 && g->precision == RAD_PHASE_F64 && n_mx >= 16) {
+        GridPart lo, mx;
+        double all = 0.0, lo_cost = 0.0;
+        (void)default_tile(g->n_dir, g->n_omega, 0, &all);
+        lo.n = g->const_k0;
+        if (lo.n > 0) lo.tile = default_tile(g->n_dir, lo.n, 0, &lo_cost);
+        mx.matrix = true;
+        mx.k0 = g->const_k0;
+        mx.n = n_mx;
+        const double mx_cost = matrix_shape(g->n_dir, n_mx, &mx.rg, &mx.fgroups);
+        if (lo_cost + mx_cost < 0.9 * all) {
+            if (lo.n > 0) g->parts.push_back(lo);
+            g->parts.push_back(mx);
+            return;
+        }
+    }
+    GridPart all;
+    all.n = g->n_omega;
+    all.tile = g->tile;
+    g->parts.push_back(all);
 }
 
 int validate_tile(const rad_tile& t)
@@ -363,24 +419,24 @@ int validate_tile(const rad_tile& t)
 
 int ensure_partials(rad_grid* g)
 {
-    const int64_t need = max_splits(g);
-    if (need <= g->part_splits) return RAD_OK;
+    size_t bytes = 0;
+    for (const GridPart& p : g->parts) bytes = std::max(bytes, max_splits(g, p) * split_bytes(g, p));
+    if (bytes <= g->part_bytes) return RAD_OK;
     if (g->d_part[0] || g->d_part[1]) {
         RAD_HIP(hipDeviceSynchronize());
         for (int b = 0; b < 2; ++b) {
             if (g->d_part[b]) RAD_HIP(hipFree(g->d_part[b]));
             g->d_part[b] = nullptr;
         }
-        g->part_splits = 0;
+        g->part_bytes = 0;
     }
-    const size_t bytes = (size_t)need * g->n_omega * g->n_dir * 4 * sizeof(float);
     for (int b = 0; b < 2; ++b) {
         if (hipMalloc(&g->d_part[b], bytes) != hipSuccess) {
             g->d_part[b] = nullptr;
             return fail(RAD_ERR_OOM, "cannot allocate 2 x %zu B of partial sums", bytes);
         }
     }
-    g->part_splits = need;
+    g->part_bytes = bytes;
     return RAD_OK;
 }
 
@@ -473,8 +529,10 @@ void fill_job(rad::Job& j, const rad_grid* g, const rad_particles* p, double t0,
 // 1024 particles x 16 x 64 points 19.0 -> 8.2 us (128 workgroups of 8 waves instead of 32 of
 // one), 2000 x 2 x 241 of an explicit list 22.6 -> 10.7; 50000 x 128 x 256 of a block-stepped
 // list, 391 particles a split instead of 13 chunks in 121 of 128 splits, 380 -> 355.
+//
+// The matrix kernel's splits are whole steps of 16 particles, at least two.
 template <typename Fn>
-int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, int waves, Fn fn)
+int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, const GridPart& part, Fn fn)
 {
     const int64_t per_launch_cap = target_splits * kMaxPerWorkgroup;
     for (int64_t i0 = 0; i0 < total; i0 += per_launch_cap) {
@@ -482,10 +540,12 @@ int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, int waves,
         const int64_t n = i1 - i0;
         int64_t per = (n + target_splits - 1) / target_splits;
         int ksplit = 1;
-        if (per <= rad::kChunk) {
+        if (part.matrix) {
+            per = std::max<int64_t>(32, (per + 15) / 16 * 16);
+        } else if (per <= rad::kChunk) {
             per = rad::kChunk;
             auto fits = [&](int64_t p, int k) { return (n + p - 1) / p * k <= target_splits; };
-            while (2 * ksplit * waves <= kMaxWaves && fits(per, 2 * ksplit)) ksplit *= 2;
+            while (2 * ksplit * part.tile.waves <= kMaxWaves && fits(per, 2 * ksplit)) ksplit *= 2;
             while (per > kMinPerSplit && fits(per / 2, ksplit)) per /= 2;
         }
         const int64_t chunks = (per + rad::kChunk - 1) / rad::kChunk;
@@ -498,6 +558,45 @@ int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, int waves,
         if (int rc = fn()) return rc;
     }
     return RAD_OK;
+}
+
+// The launch of one part that for_each_launch prepared in `a`.
+hipError_t launch_part(const rad_grid* g, const AccArgs& a, const GridPart& part, int dtype, hipStream_t st,
+                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
+{
+    if (!part.matrix)
+        return rad::launch_accumulate(a, dtype, g->precision, shape_of(part.tile, g->variant),
+                                      a.splits * tiles_of(g, part), st, e0, e1);
+    rad::MxArgs m{};
+    m.job = a.job;
+    m.part = a.part;
+    m.g = g->const_g.x;
+    m.g1 = g->const_g.y;
+    m.k0 = part.k0;
+    m.n_sub = part.n;
+    m.fgroups = part.fgroups;
+    m.splits = a.splits;
+    m.per_split = a.per_split;
+    return rad::launch_accumulate_mx(m, dtype, part.rg, st, e0, e1);
+}
+
+// Adds a launch's partial sums to the part's range of S ([omega][dir]: a contiguous one).
+hipError_t fold_part(const rad_grid* g, const AccArgs& a, const GridPart& part, hipStream_t st,
+                     hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
+{
+    return rad::launch_fold(a.part, g->d_S + (int64_t)part.k0 * g->n_dir * 4, a.splits, (int64_t)part.n * g->n_dir * 4,
+                            st, e0, e1);
+}
+
+// The job of one part: the general kernel sees the frequencies below the part's end.
+void part_job(rad::Job& j, const rad_grid* g, const GridPart& part, const rad_particles* p, double t0,
+              int64_t n_per_step)
+{
+    fill_job(j, g, p, t0, n_per_step, part.matrix ? g->tile : part.tile);
+    if (part.matrix) return;
+    const int to = rad::tile_omegas(shape_of(part.tile));
+    j.n_omega = part.n;
+    j.tiles_w = (part.n + to - 1) / to;
 }
 
 // Work marked on one stream is ordered before later work on another by an event; work on
@@ -528,51 +627,58 @@ hipError_t mark_done(rad_grid::Mark& m, hipStream_t st, hipEvent_t stamped = nul
     return m.recorded && !stamped ? hipEventRecord(m.ev, st) : hipSuccess;
 }
 
+// One launch of a push (accumulate and fold) of one part, as for_each_launch prepared it.
+int push_launch(rad_grid* g, const GridPart& part, AccArgs& a, int dtype, hipStream_t st, bool timed_push)
+{
+    const int b = g->part_next;
+    g->part_next ^= 1;
+    a.part = g->d_part[b];
+    // the fold that last read this buffer must be done before it is overwritten
+    RAD_HIP(order_after(g->part_read[b], st));
+    hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr, e3 = nullptr;
+    // a grid of two parts times both launches of a push, or neither
+    if (timed_push || (g->profiling && g->parts.size() == 1 && g->prof_count++ % g->prof_period == 0)) {
+        RAD_HIP(take_event(g, &e0));
+        RAD_HIP(take_event(g, &e1));
+        RAD_HIP(take_event(g, &e2));
+        RAD_HIP(take_event(g, &e3));
+        g->ev_acc.emplace_back(e0, e1);
+        g->ev_fold.emplace_back(e2, e3);
+        g->prof_updates += (a.job.i_end - a.job.i_begin) * (int64_t)g->n_dir * part.n;
+    }
+    hipError_t e = launch_part(g, a, part, dtype, st, e0, e1);
+    if (e != hipSuccess) return hip_fail(e, "accumulate launch");
+    // The fold runs right after the accumulate on the caller's stream, so it has the
+    // whole GPU for its few microseconds (beside the next push's accumulate it would
+    // trickle along in the few free wave slots), and after every write of S already issued
+    // on another stream.  Where an event is needed (another stream than the null stream)
+    // the fold's launch stamps it, without a marker between this fold and the next push's
+    // accumulate; a timed fold stamps its timing event, and the mark is recorded after it.
+    RAD_HIP(order_after(g->last_write, st));
+    const hipEvent_t stamp = e3 || !st ? nullptr : g->part_read[b].own;
+    e = fold_part(g, a, part, st, e2, e3 ? e3 : stamp);
+    if (e != hipSuccess) return hip_fail(e, "fold launch");
+    RAD_HIP(mark_done(g->part_read[b], st, stamp));
+    RAD_HIP(mark_done(g->last_write, st, st ? g->part_read[b].own : nullptr));
+    return RAD_OK;
+}
+
 // Accumulate particles [0, total) (step of element i is i / n_per_step, t = t0 + step*dt).
 int push_range(rad_grid* g, double t0, int64_t n_per_step, int64_t total, const rad_particles* p,
                hipStream_t st)
 {
     int rc = ensure_partials(g);
     if (rc) return rc;
-    const LaunchShape ls = shape_of(g->tile, g->variant);
-    const int td = tiles_d(g), tw = tiles_w(g), nt = td * tw;
-    const int64_t count = (int64_t)g->n_omega * g->n_dir * 4;
-    const int64_t target_splits = max_splits(g);   // <= part_splits (capacity may be larger)
-    AccArgs a{};
-    fill_job(a.job, g, p, t0, n_per_step, g->tile);
-    return for_each_launch(a, total, target_splits, ls.waves, [&]() -> int {
-        const int64_t i0 = a.job.i_begin, i1 = a.job.i_end, splits = a.splits;
-        const int b = g->part_next;
-        g->part_next ^= 1;
-        a.part = g->d_part[b];
-        // the fold that last read this buffer must be done before it is overwritten
-        RAD_HIP(order_after(g->part_read[b], st));
-        hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr, e3 = nullptr;
-        if (g->profiling && g->prof_count++ % g->prof_period == 0) {
-            RAD_HIP(take_event(g, &e0));
-            RAD_HIP(take_event(g, &e1));
-            RAD_HIP(take_event(g, &e2));
-            RAD_HIP(take_event(g, &e3));
-            g->ev_acc.emplace_back(e0, e1);
-            g->ev_fold.emplace_back(e2, e3);
-            g->prof_updates += (i1 - i0) * (int64_t)g->n_dir * g->n_omega;
-        }
-        hipError_t e = rad::launch_accumulate(a, p->dtype, g->precision, ls, (int)(splits * nt), st, e0, e1);
-        if (e != hipSuccess) return hip_fail(e, "accumulate launch");
-        // The fold runs right after the accumulate on the caller's stream, so it has the
-        // whole GPU for its few microseconds (beside the next push's accumulate it would
-        // trickle along in the few free wave slots), and after every write of S already issued
-        // on another stream.  Where an event is needed (another stream than the null stream)
-        // the fold's launch stamps it, without a marker between this fold and the next push's
-        // accumulate; a timed fold stamps its timing event, and the mark is recorded after it.
-        RAD_HIP(order_after(g->last_write, st));
-        const hipEvent_t stamp = e3 || !st ? nullptr : g->part_read[b].own;
-        e = rad::launch_fold(g->d_part[b], g->d_S, (int)splits, count, st, e2, e3 ? e3 : stamp);
-        if (e != hipSuccess) return hip_fail(e, "fold launch");
-        RAD_HIP(mark_done(g->part_read[b], st, stamp));
-        RAD_HIP(mark_done(g->last_write, st, st ? g->part_read[b].own : nullptr));
-        return RAD_OK;
-    });
+    const bool timed_push = g->profiling && g->parts.size() > 1 && g->prof_count++ % g->prof_period == 0;
+    for (const GridPart& part : g->parts) {
+        AccArgs a{};
+        part_job(a.job, g, part, p, t0, n_per_step);
+        rc = for_each_launch(a, total, max_splits(g, part), part, [&]() -> int {
+            return push_launch(g, part, a, p->dtype, st, timed_push);
+        });
+        if (rc) return rc;
+    }
+    return RAD_OK;
 }
 
 int read_err_flag(rad_grid* g, hipStream_t st, int* flag)
@@ -760,6 +866,7 @@ int rad_create_grid(rad_grid** out, const rad_grid_desc* d)
     g->variant = tb.variant;
     g->domega = tb.domega;
     g->tile = default_tile(d->n_dir, d->n_omega, g->variant);
+    g->const_k0 = d->n_omega;
 
     std::vector<double>& om = tb.om;
     std::vector<float2> gt((size_t)d->n_omega);
@@ -767,6 +874,13 @@ int rad_create_grid(rad_grid** out, const rad_grid_desc* d)
         const double gg = is_shape3(d->shape) ? 0.0 : shape_factor(d->shape, d->shape_len, om[k]);
         gt[k] = make_float2((float)gg, (float)(1.0 - gg));
     }
+    if (!is_shape3(d->shape)) {
+        int k = d->n_omega - 1;
+        while (k > 0 && gt[k - 1].x == gt[k].x && gt[k - 1].y == gt[k].y) --k;
+        g->const_k0 = std::min(d->n_omega, (k + 15) / 16 * 16);
+        g->const_g = gt[d->n_omega - 1];
+    }
+    plan_parts(g);
     std::vector<float> g3;
     if (is_shape3(d->shape)) {
         g3.resize((size_t)points);
@@ -875,12 +989,11 @@ int rad_push_step_noalloc(rad_grid* g, double t, int64_t n_particles, const rad_
     int rc = check_particles(p);
     if (rc) return rc;
     const int64_t count = (int64_t)g->n_omega * g->n_dir * 4;        // FP32 values per split
-    const int64_t split_bytes = count * (int64_t)sizeof(float);
-    const int64_t cap_splits = (int64_t)(RAD_NOALLOC_SCRATCH_BYTES / (size_t)split_bytes);
-    if (cap_splits < 1)
+    const int64_t grid_bytes = count * (int64_t)sizeof(float);
+    if (grid_bytes > (int64_t)RAD_NOALLOC_SCRATCH_BYTES)
         return fail(RAD_ERR_INVALID_ARG,
                     "grid of %lld points needs %lld B of partial sums, more than the %zu B no-allocation "
-                    "scratch (at most %zu points)", (long long)(count / 4), (long long)split_bytes,
+                    "scratch (at most %zu points)", (long long)(count / 4), (long long)grid_bytes,
                     (size_t)RAD_NOALLOC_SCRATCH_BYTES, (size_t)RAD_NOALLOC_SCRATCH_BYTES / 16);
     DeviceGuard dg(g->device);
     float* scr = g->device >= 0 && g->device < kScratchDevices
@@ -896,21 +1009,22 @@ int rad_push_step_noalloc(rad_grid* g, double t, int64_t n_particles, const rad_
     // every fold of this grid runs in issue order: the folds below come after every fold
     // already issued (on any stream), later folds, read-outs and resets after them
     if (!capturing) RAD_HIP(order_after(g->last_write, st));
-    const LaunchShape ls = shape_of(g->tile, g->variant);
-    const int nt = tiles_d(g) * tiles_w(g);
-    AccArgs a{};
-    fill_job(a.job, g, p, t, n_particles, g->tile);
-    a.part = scr;
-    rc = for_each_launch(a, n_particles, std::min<int64_t>(max_splits(g), cap_splits), ls.waves, [&]() -> int {
-        // same stream: a launch's accumulate rewrites the scratch only after the previous
-        // launch's fold has read it
-        hipError_t e = rad::launch_accumulate(a, p->dtype, g->precision, ls, (int)(a.splits * nt), st);
-        if (e != hipSuccess) return hip_fail(e, "accumulate launch");
-        e = rad::launch_fold(scr, g->d_S, a.splits, count, st);
-        if (e != hipSuccess) return hip_fail(e, "fold launch");
-        return RAD_OK;
-    });
-    if (rc) return rc;
+    for (const GridPart& part : g->parts) {
+        AccArgs a{};
+        part_job(a.job, g, part, p, t, n_particles);
+        a.part = scr;
+        const int64_t cap = (int64_t)(RAD_NOALLOC_SCRATCH_BYTES / split_bytes(g, part));
+        rc = for_each_launch(a, n_particles, std::min<int64_t>(max_splits(g, part), cap), part, [&]() -> int {
+            // same stream: a launch's accumulate rewrites the scratch only after the previous
+            // launch's fold has read it
+            hipError_t e = launch_part(g, a, part, p->dtype, st);
+            if (e != hipSuccess) return hip_fail(e, "accumulate launch");
+            e = fold_part(g, a, part, st);
+            if (e != hipSuccess) return hip_fail(e, "fold launch");
+            return RAD_OK;
+        });
+        if (rc) return rc;
+    }
     if (!capturing) RAD_HIP(mark_done(g->last_write, st));
     return RAD_OK;
 }
@@ -1003,8 +1117,12 @@ int rad_set_tile(rad_grid* g, const rad_tile* t)
     DeviceGuard dg(g->device);
     const rad_tile old = g->tile;
     g->tile = *t;
+    plan_parts(g);
     rc = ensure_partials(g);
-    if (rc) g->tile = old;
+    if (rc) {
+        g->tile = old;
+        plan_parts(g);
+    }
     return rc;
 }
 
