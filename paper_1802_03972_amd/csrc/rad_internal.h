@@ -53,18 +53,20 @@ struct AccArgs {
 };
 
 // Arguments of the matrix-core accumulate kernel: frequencies [k0, k0 + n_sub) of the job's grid,
-// all with the shape factor g (g1 = 1 - g), in fgroups groups of rg x 256; one wave for each
-// (particle split, frequency group, direction).
+// all with the shape factor g (g1 = 1 - g) but the first `head` of them (at most kMxHead, and only
+// with k0 = 0), in fgroups groups of rg x 256; one wave for each (particle split, frequency
+// group, direction).
 struct MxArgs {
     Job job;
     float* part;            // [splits][n_sub][n_dir][4]
     float g, g1;
-    int32_t k0, n_sub;
+    int32_t k0, n_sub, head;
     int32_t fgroups;
     int32_t splits;
     int64_t per_split;
 };
 constexpr int kMxBlock = 256;   // frequencies of a row group
+constexpr int kMxHead = 4;
 
 // Batched launch: every workgroup walks its own list of segments; a segment is a chunk
 // range of one (item, tile) and owns one partial tile [TO][TD][4] in the segment buffer.

@@ -22,9 +22,18 @@
 //   64 particles at a time, each lane computes one particle's geometry (FP64, as in the general
 //   kernel) into the wave's own LDS, then four steps of 16 particles.  Consecutive waves take
 //   consecutive directions, so that their 16-byte partial sums fill lines.
+// * Head.  A wide grid's Gaussian differs from its constant at the first frequency or two only.
+//   Up to kMxHead of them are summed apart, each lane over its particles (weight, FP64 phase and
+//   two complex multiply-adds per particle and frequency, kept in LDS), and replace the
+//   matrix product's values there: as a launch of the general kernel over a block of 16
+//   the first of 1024 frequencies cost 570 us beside the 3430 of the others; this way 3250 us
+//   for all (16384 particles x 32 steps x 64 directions).
 // * Bound by the VALU: per 16 particles about 510 cycles for the columns and 320 for each 256
 //   frequencies' rows, half of it the splits, plus 20 for each of the 12 matrix instructions.
-//   RAD_MX_FIG
+//   200000 particles x 64 directions: 512 frequencies 9.6e12 terms/s, 1024 frequencies 1.1e13;
+//   128 x 256 7.6e12; the general kernel's walk 4.3e12 to 5.3e12.  With four row groups two
+//   waves per SIMD are enough (more, of fewer rows, recompute the columns: 7.6e12 and 9.7e12
+//   with one and two row groups on 1024 frequencies).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -87,6 +96,7 @@ template <typename InT, int RG>
 __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxArgs a)
 {
     __shared__ MxParticle buf_all[kMxThreads];
+    extern __shared__ float4 head_all[];                   // [head][threads]
     const Job& j = a.job;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -108,6 +118,10 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
     const double quarter_row = (r & 1) ? 0.0 : 0.25;        // even rows cos, odd rows sin
     const double om_col = (double)(r & 15) * j.domega;
     const double quarter_col = r < 16 ? 0.25 : 0.0;         // columns 0..15 cos, 16..31 sin
+
+    const int head = fg == 0 ? a.head : 0;
+    float4* hsum = head_all + threadIdx.x;
+    for (int k = 0; k < head; ++k) hsum[k * kMxThreads] = make_float4(0.f, 0.f, 0.f, 0.f);
 
     f32x16 acc[RG][2];
 #pragma unroll
@@ -141,6 +155,20 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
             e.ph = ok ? ph : 0.0;
             e.a1 = ok ? F * geo.x : 0.f;
             e.a2 = ok ? F * geo.y : 0.f;
+            for (int k = 0; k < head; ++k) {
+                const float g0 = gload(reinterpret_cast<const float*>(j.gtab), 2 * (int64_t)k);
+                const float g1 = gload(reinterpret_cast<const float*>(j.gtab), 2 * (int64_t)k + 1);
+                const float Fk = ok ? __builtin_amdgcn_sqrtf(fmaf(N * N, g0, N * g1)) : 0.f;
+                float zr, zi;
+                sincos_rev_fast(static_cast<float>(frac_rev(gload(j.omega, k) * ph)), zi, zr);
+                const float ur = Fk * zr, ui = Fk * zi;
+                float4 v = hsum[k * kMxThreads];
+                v.x = fmaf(geo.x, ur, v.x);
+                v.y = fmaf(geo.x, ui, v.y);
+                v.z = fmaf(geo.y, ur, v.z);
+                v.w = fmaf(geo.y, ui, v.w);
+                hsum[k * kMxThreads] = v;
+            }
             wave_lds_sync();                               // the last 64's reads are done
             buf[lane] = e;
         }
@@ -216,8 +244,19 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
             const float4 v = is_cos ? make_float4(sv[0][0], t0, sv[0][1], t1) : make_float4(t0, sv[1][0], t1, sv[1][1]);
             const int q = 4 * (i / 4) + 2 * half + (is_cos ? 0 : 1);
             const int k = ((fg * RG + g) * 16 + q) * 16 + (r & 15);
-            if (k < a.n_sub) out[(int64_t)k * j.n_dir] = v;
+            if (k < a.n_sub && k >= head) out[(int64_t)k * j.n_dir] = v;
         }
+    }
+    for (int k = 0; k < head; ++k) {
+        float4 v = hsum[k * kMxThreads];
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) {
+            v.x += __shfl_xor(v.x, m);
+            v.y += __shfl_xor(v.y, m);
+            v.z += __shfl_xor(v.z, m);
+            v.w += __shfl_xor(v.w, m);
+        }
+        if (lane == 0) out[(int64_t)k * j.n_dir] = v;
     }
 }
 
@@ -227,13 +266,15 @@ hipError_t launch_mx_t(const MxArgs& a, int rg, hipStream_t st, hipEvent_t ev_st
     const int64_t waves = (int64_t)a.splits * a.fgroups * a.job.n_dir;
     constexpr int per = kMxThreads / 64;
     const dim3 grid((unsigned)((waves + per - 1) / per)), block(kMxThreads);
+    const size_t lds = (size_t)a.head * kMxThreads * sizeof(float4);
     auto go = [&](auto kern) -> hipError_t {
         if (ev_start || ev_stop) {
             MxArgs arg = a;
             void* args[] = {&arg};
-            return hipExtLaunchKernel(reinterpret_cast<const void*>(kern), grid, block, args, 0, st, ev_start, ev_stop, 0);
+            return hipExtLaunchKernel(reinterpret_cast<const void*>(kern), grid, block, args, lds, st, ev_start,
+                                      ev_stop, 0);
         }
-        hipLaunchKernelGGL(kern, grid, block, 0, st, a);
+        hipLaunchKernelGGL(kern, grid, block, lds, st, a);
         return hipGetLastError();
     };
     switch (rg) {

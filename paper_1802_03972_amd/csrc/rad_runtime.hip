@@ -231,7 +231,8 @@ struct GridPart {
     int k0 = 0, n = 0;        // frequencies [k0, k0 + n)
     bool matrix = false;      // matrix-core kernel (k0 and all below: the general one)
     rad_tile tile{};          // general kernel's launch shape
-    int rg = 0, fgroups = 0;  // matrix kernel: row groups per wave, frequency groups
+    int rg = 0, fgroups = 0;  // matrix kernel: row groups per wave, frequency groups, and
+    int head = 0;             // the first frequencies that it sums apart
 };
 
 struct rad_grid {
@@ -267,8 +268,8 @@ struct rad_grid {
     float* d_g3 = nullptr;     // [n_dir][n_omega] for 3-D shapes
     double* d_bstep = nullptr; // per-block spacing of a piecewise-uniform frequency list
     int variant = 0;           // rad::kVarDirect | rad::kVarShape3
-    int const_k0 = 0;          // from this frequency on (a multiple of 16; n_omega: none) the
-    float2 const_g{};          // shape table holds one pair (g, 1 - g)
+    int const_k0 = 0;          // from this frequency on (n_omega: none) the shape table holds
+    float2 const_g{};          // one pair (g, 1 - g)
     std::vector<GridPart> parts;
     bool counted = false;      // among the users of the read-out buffers
     // kernel timing (rad_profile_*)
@@ -372,24 +373,27 @@ double matrix_shape(int n_dir, int n, int* rg, int* fgroups)
 }
 
 // Which kernel accumulates which frequencies.  The matrix kernel takes the frequencies over
-// which the shape factor is one constant (the end of the grid from a multiple of 16 on) where
-// its waves of 256 frequencies of one direction cost less than the general kernel's tiles:
-// from about 150 frequencies on, from fewer for directions that fill a tile badly.  RAD_MX_LINE
+// which the shape factor is one constant, and up to kMxHead before them; with more before
+// them the general kernel takes those, in whole blocks of 16.  It is used where its waves of
+// 256 frequencies of one direction cost less than the general kernel's tiles: from about 150
+// frequencies on, from fewer for directions that fill a tile badly (both sides at 0.9: 256
+// frequencies 0.82 ms against 1.54 for 200000 particles x 128 directions; with half of a
+// wave's 256 in the grid the two are equal).
 void plan_parts(rad_grid* g)
 {
     g->parts.clear();
-    const int n_mx = g->n_omega - g->const_k0;
-    if (g->variant == 0 && g->precision == RAD_PHASE_F64 && n_mx >= 16) {
-        GridPart lo, mx;
-        double all = 0.0, lo_cost = 0.0;
-        (void)default_tile(g->n_dir, g->n_omega, 0, &all);
-        lo.n = g->const_k0;
+    GridPart lo, mx;
+    mx.matrix = true;
+    mx.head = g->const_k0 <= rad::kMxHead ? g->const_k0 : 0;
+    mx.k0 = mx.head ? 0 : (g->const_k0 + 15) / 16 * 16;
+    mx.n = g->n_omega - mx.k0;
+    if (g->variant == 0 && g->precision == RAD_PHASE_F64 && mx.n >= 16 && g->const_k0 < g->n_omega) {
+        double all_cost = 0.0, lo_cost = 0.0;
+        (void)default_tile(g->n_dir, g->n_omega, 0, &all_cost);
+        lo.n = mx.k0;
         if (lo.n > 0) lo.tile = default_tile(g->n_dir, lo.n, 0, &lo_cost);
-        mx.matrix = true;
-        mx.k0 = g->const_k0;
-        mx.n = n_mx;
-        const double mx_cost = matrix_shape(g->n_dir, n_mx, &mx.rg, &mx.fgroups);
-        if (lo_cost + mx_cost < 0.9 * all) {
+        const double mx_cost = matrix_shape(g->n_dir, mx.n, &mx.rg, &mx.fgroups);
+        if (lo_cost + mx_cost < 0.9 * all_cost) {
             if (lo.n > 0) g->parts.push_back(lo);
             g->parts.push_back(mx);
             return;
@@ -574,6 +578,7 @@ hipError_t launch_part(const rad_grid* g, const AccArgs& a, const GridPart& part
     m.g1 = g->const_g.y;
     m.k0 = part.k0;
     m.n_sub = part.n;
+    m.head = part.head;
     m.fgroups = part.fgroups;
     m.splits = a.splits;
     m.per_split = a.per_split;
@@ -877,7 +882,7 @@ int rad_create_grid(rad_grid** out, const rad_grid_desc* d)
     if (!is_shape3(d->shape)) {
         int k = d->n_omega - 1;
         while (k > 0 && gt[k - 1].x == gt[k].x && gt[k - 1].y == gt[k].y) --k;
-        g->const_k0 = std::min(d->n_omega, (k + 15) / 16 * 16);
+        g->const_k0 = k;
         g->const_g = gt[d->n_omega - 1];
     }
     plan_parts(g);

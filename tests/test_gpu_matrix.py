@@ -68,6 +68,15 @@ def test_gauss_in_two_parts(rad, n_omega, omega_max, dtype):
     check(rad, 333, 3, 5, n_omega, shape="gauss", dtype=dtype, omega_max=omega_max)
 
 
+# 1 to 4 first frequencies beside the constant are summed apart, with 5 the general kernel takes 16;
+# exp(-(omega L / c)^2) is zero in FP32 from omega L / c = 10.2 on
+@pytest.mark.parametrize("n_omega", [256, 600])
+@pytest.mark.parametrize("first", [1, 2, 3, 4, 5, 17])
+def test_gauss_heads(rad, first, n_omega):
+    step = 10.2 * 299792458.0 / 1e-7 / (first - 0.5)
+    check(rad, 150, 3, 1, n_omega, shape="gauss", omega_max=step * (n_omega - 1))
+
+
 @pytest.mark.parametrize("shape", ["point", "gauss"])
 def test_steps_offsets_and_first_frequency(rad, shape):
     check(rad, 123, 3, 3, 520, shape=shape, dtype="f64", steps=5, t0=1e-12)
