@@ -96,6 +96,7 @@ struct TrackedArgs {
     const double* omega;
     double domega;
     double* T;              // [n_particles][n_omega][n_dir][4] FP64
+    bool T_zero;            // T holds zeros
     int* err;
     int32_t n_dir, n_omega;
 };

@@ -1727,6 +1727,10 @@ struct rad_tracked {
     double* d_dirs9 = nullptr;
     double* d_omega = nullptr;
     double* d_T = nullptr;
+    // d_T holds zeros when the work issued so far has run: the next push need not read it.
+    // What a captured graph does to it is not seen here, so a capture ends the use of this.
+    bool T_zero = false;
+    bool captured = false;
     double* d_wg = nullptr;    // n_particles weights, then up to n_dir * n_omega shape factors
     double* d_I = nullptr;
     bool counted = false;      // among the users of the read-out buffers
@@ -1794,6 +1798,7 @@ extern "C" int rad_tracked_create(rad_tracked** out, const rad_grid_desc* d, int
     }
     stages().retain();
     tr->counted = true;
+    tr->T_zero = true;
     *out = tr;
     return RAD_OK;
 }
@@ -1809,6 +1814,21 @@ extern "C" int rad_tracked_destroy(rad_tracked* tr)
     return RAD_OK;
 }
 
+namespace {
+
+int note_capture(rad_tracked* tr, hipStream_t st)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    RAD_HIP(hipStreamIsCapturing(st, &cap));
+    if (cap != hipStreamCaptureStatusNone) {
+        tr->captured = true;
+        tr->T_zero = false;
+    }
+    return RAD_OK;
+}
+
+}  // namespace
+
 extern "C" int rad_tracked_reset(rad_tracked* tr, void* stream)
 {
     if (!tr) return fail(RAD_ERR_INVALID_ARG, "tracked is NULL");
@@ -1816,6 +1836,8 @@ extern "C" int rad_tracked_reset(rad_tracked* tr, void* stream)
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = rad::launch_reset(tr->d_T, tr->n_particles * tr->n_dir * tr->n_omega * 4, tr->d_err, st);
     if (e != hipSuccess) return hip_fail(e, "tracked reset");
+    if (int rc = note_capture(tr, st)) return rc;
+    tr->T_zero = !tr->captured;
     return RAD_OK;
 }
 
@@ -1844,7 +1866,10 @@ int tracked_push(rad_tracked* tr, double t0, int32_t n_steps, const rad_particle
     a.dirs9 = tr->d_dirs9;
     a.omega = tr->d_omega;
     a.domega = tr->domega;
+    if ((rc = note_capture(tr, (hipStream_t)stream))) return rc;
     a.T = tr->d_T;
+    a.T_zero = tr->T_zero;
+    tr->T_zero = false;
     a.err = tr->d_err;
     a.n_dir = tr->n_dir;
     a.n_omega = tr->n_omega;
