@@ -51,36 +51,47 @@ namespace {
 // to out[o * row + d] (as (S1r, S1i, S2r, S2i)) when it lies inside the grid.  Every thread of
 // the workgroup must call this with the same arguments; LDS is reused chunk by chunk.
 //
-// KSPLIT: the workgroup's waves are `groups` (a power of two) groups that cover the tile once
-// each and take every groups-th particle of a chunk; their sums are added through LDS at the
-// end.  A push too small for the chip's waves is a serial chain of particles in each of a few
-// waves; the groups shorten the chain without more partial tiles to fold.  A build of its
-// own, as the group's index costs the large pushes' kernel registers that it has not got.
-template <typename InT, int PREC, int W, int DPW, int V, bool KSPLIT>
+// DPW = 0 is the flexible build, whose lanes are laid out at run time (FlexShape): a tile of any
+// number of directions x blocks of W frequencies, one (direction, block) pair per lane; where
+// the pairs do not fill a wave, `slots` sets of lanes hold them and take particles in turn; and
+// `groups` (a power of two) sets of waves do the same.  The sums of slots and groups are added
+// at the end, through shuffles and LDS.  It serves
+// * pushes too small for the chip's waves, which would be serial chains of particles in a few
+//   waves: groups shorten the chain without more partial tiles to fold;
+// * grids of fewer than 16 directions, of which the other builds' tiles are mostly empty.
+// A build of its own, as what it keeps costs the others registers that they have not got.
+template <typename InT, int PREC, int W, int DPW, int V>
 __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, int64_t p_begin,
-                                                 int64_t p_end, int chunk, int groups,
+                                                 int64_t p_end, int chunk, const FlexShape& fx,
                                                  float4* __restrict__ out, int row, float4* smem4)
 {
-    constexpr int P = kChunk;
-    constexpr int SUBS = 64 / DPW;
-    constexpr int TD = DPW;
+    constexpr bool FLEX = DPW == 0;
+    constexpr int P = FLEX ? kFlexChunk : kChunk;
+    constexpr int SUBS = FLEX ? 1 : 64 / (FLEX ? 64 : DPW);
     static_assert(W % 4 == 0, "W must be a multiple of 4");
 
+    const int TD = FLEX ? fx.dirs : DPW;
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
-    const int waves = KSPLIT ? (nt >> 6) / groups : nt >> 6;   // waves that cover the tile
-    const int TO = waves * SUBS * W;
+    const int waves = FLEX ? (nt >> 6) / fx.groups : nt >> 6;   // waves that cover the tile
+    const int TO = FLEX ? fx.blocks * W : waves * SUBS * W;
+    const int row_f = FLEX ? fx.blocks * fx.block_stride : TO;  // F table: one particle's row
     const int lane = tid & 63;
-    const int group = KSPLIT ? __builtin_amdgcn_readfirstlane(tid >> 6) / waves : 0;
+    // flexible build: this wave's group and slots, the lane's pair
+    const int group = FLEX ? __builtin_amdgcn_readfirstlane(tid >> 6) / waves : 0;
     const int wave = (tid >> 6) - group * waves;
-    const int dl = lane % DPW;
-    const int ob = wave * SUBS + lane / DPW;
+    const int slot_lanes = FLEX ? 64 / fx.slots : 64;
+    const int slot = FLEX ? lane / slot_lanes : 0;
+    const int pair = wave * slot_lanes + lane - slot * slot_lanes;
+    const bool live = !FLEX || pair < TD * fx.blocks;
+    const int ob = !live ? 0 : FLEX ? pair / TD : wave * SUBS + lane / (FLEX ? 64 : DPW);
+    const int dl = !live ? 0 : FLEX ? pair - ob * TD : lane % (FLEX ? 64 : DPW);
 
-    float4* geo = smem4;                                             // [P][TD]
-    double* taus = reinterpret_cast<double*>(geo + P * TD);          // [P][TD]
-    double* raw = taus + P * TD;                                     // [11][P]
+    float4* geo = smem4;                                             // [P][TD] (flexible: [chunk][TD])
+    double* taus = reinterpret_cast<double*>(geo + (FLEX ? chunk : P) * TD);
+    double* raw = taus + (FLEX ? chunk : P) * TD;                    // [11][P]
     float2* nw = reinterpret_cast<float2*>(raw + 11 * P);            // [P]: (N, N^2) in FP32
-    float* ff = reinterpret_cast<float*>(nw + P);                    // [P][TO]
+    float* ff = reinterpret_cast<float*>(nw + P);                    // [P][row_f]
 
     constexpr bool DIRECT = (V & kVarDirect) != 0;
     constexpr bool SHAPE3 = (V & kVarShape3) != 0;
@@ -151,15 +162,16 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
             dg = dg < j.n_dir ? dg : j.n_dir - 1;
             float4 gv;
             double ph;
-            particle_direction_setup<PREC, !DIRECT && !BSTEP>(raw, m, j.dirs9 + 9 * dg, j.domega, gv, ph, j.err);
+            particle_direction_setup<PREC, !DIRECT && !BSTEP, P>(raw, m, j.dirs9 + 9 * dg, j.domega, gv, ph, j.err);
             geo[i] = gv;
             taus[i] = ph;
         }
         // 3. per (particle, frequency) form-factor weight F = sqrt(N^2 g + N (1 - g)) (Eq. 12),
-        //    FP32; frequencies outside the grid get F = 0 and contribute nothing.  With groups
-        //    there are several threads for each frequency, which take the particles in turn.
-        const int f_step = KSPLIT ? (nt > TO ? nt / TO : 1) : 1;
-        const int f_first = KSPLIT && f_step > 1 ? tc / TO : 0;
+        //    FP32; frequencies outside the grid get F = 0 and contribute nothing.  The flexible
+        //    build has several threads for a frequency, which take the particles in turn, and
+        //    may keep the blocks' rows apart (narrow tiles read many blocks at once).
+        const int f_step = FLEX ? (nt > TO ? nt / TO : 1) : 1;
+        const int f_first = FLEX && f_step > 1 ? tc / TO : 0;
         for (int o = tc - f_first * TO; o < (SHAPE3 || f_first >= f_step ? 0 : TO); o += nt) {
             const int og = tw * TO + o;
             float2 g = make_float2(0.f, 0.f);
@@ -167,9 +179,9 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
                 const float* gt = reinterpret_cast<const float*>(j.gtab);
                 g = make_float2(gload(gt, 2 * (int64_t)og), gload(gt, 2 * (int64_t)og + 1));
             }
-            float* dst = ff + o + f_first * TO;
+            float* dst = ff + (FLEX ? o / W * fx.block_stride + o % W : o) + f_first * row_f;
 #pragma unroll 8
-            for (int m = f_first; m < cnt; m += f_step, dst += f_step * TO) {
+            for (int m = f_first; m < cnt; m += f_step, dst += f_step * row_f) {
                 const float2 N = nw[m];
                 const float Fo = __builtin_amdgcn_sqrtf(fmaf(N.y, g.x, N.x * g.y));
                 *dst = (TT && (o & 2)) ? -Fo : Fo;   // sigma_k of the three-term walk
@@ -178,8 +190,19 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
         __syncthreads();
         __builtin_amdgcn_s_setprio(1);
         // 4. hot loop.
-        for (int m = group; m < cnt; m += KSPLIT ? groups : 1) {
-            const float4 gm = geo[m * TD + dl];
+        for (int m0 = FLEX ? group * fx.slots : 0; m0 < cnt; m0 += FLEX ? fx.groups * fx.slots : 1) {
+            int m = m0;
+            bool past = false;                   // this lane's slot has no particle in the last round
+            if constexpr (FLEX) {
+                m += slot;
+                past = m >= cnt;
+                m = past ? cnt - 1 : m;
+            }
+            float4 gm = geo[m * TD + dl];
+            if constexpr (FLEX) {
+                gm.x = past ? 0.f : gm.x;
+                gm.y = past ? 0.f : gm.y;
+            }
             const double ph = taus[m * TD + dl];
             float zr = 1.f, zi = 0.f;
             if constexpr (!DIRECT) {
@@ -203,7 +226,7 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
                     sincos_rev_fast(rw, wi, wr);
                 }
             }
-            const float4* fq = reinterpret_cast<const float4*>(ff + m * TO + ob * W);
+            const float4* fq = reinterpret_cast<const float4*>(ff + m * row_f + ob * (FLEX ? fx.block_stride : W));
             float Nm = 0.f, NN1 = 0.f;
             if constexpr (SHAPE3) {
                 const float2 Nv = nw[m];
@@ -360,28 +383,43 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
     //    from an opaque thread index for the same reason as the set-up's offsets.
     int te = threadIdx.x;
     asm volatile("" : "+v"(te));
-    const int dl_e = (te & 63) % DPW;
-    const int o_loc = (((te >> 6) - group * waves) * SUBS + (te & 63) / DPW) * W;
-    if constexpr (KSPLIT) {
-        // the groups' sums: the upper half of them hands its accumulators to the lower half
-        for (int half = groups >> 1; half > 0; half >>= 1) {
-            float4* slot = smem4 + ((te >> 6) - (group >= half ? half * waves : 0)) * W * 64 + (te & 63);
+    int dl_e, o_loc;
+    bool write = true;
+    if constexpr (FLEX) {
+        // the slots' sums, then the groups': the upper half hands its accumulators to the lower
+        for (int m = slot_lanes; m < 64; m <<= 1) {
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                s1r[k] += __shfl_xor(s1r[k], m);
+                s1i[k] += __shfl_xor(s1i[k], m);
+                s2r[k] += __shfl_xor(s2r[k], m);
+                s2i[k] += __shfl_xor(s2i[k], m);
+            }
+        }
+        for (int half = fx.groups >> 1; half > 0; half >>= 1) {
+            float4* share = smem4 + ((te >> 6) - (group >= half ? half * waves : 0)) * W * 64 + (te & 63);
             if (group >= half && group < 2 * half) {
 #pragma unroll
-                for (int k = 0; k < W; ++k) slot[k * 64] = make_float4(s1r[k], s1i[k], s2r[k], s2i[k]);
+                for (int k = 0; k < W; ++k) share[k * 64] = make_float4(s1r[k], s1i[k], s2r[k], s2i[k]);
             }
             __syncthreads();
             if (group < half) {
 #pragma unroll
                 for (int k = 0; k < W; ++k) {
-                    const float4 v = slot[k * 64];
+                    const float4 v = share[k * 64];
                     s1r[k] += v.x; s1i[k] += v.y; s2r[k] += v.z; s2i[k] += v.w;
                 }
             }
             __syncthreads();
         }
+        write = group == 0 && slot == 0 && live;
+        dl_e = dl;
+        o_loc = ob * W;
+    } else {
+        dl_e = (te & 63) % DPW;
+        o_loc = ((te >> 6) * SUBS + (te & 63) / DPW) * W;
     }
-    if (group == 0 && td * TD + dl_e < j.n_dir) {
+    if (write && td * TD + dl_e < j.n_dir) {
 #pragma unroll
         for (int k = 0; k < W; ++k) {
             if (tw * TO + o_loc + k < j.n_omega)
@@ -419,12 +457,13 @@ constexpr int min_waves(int W, int V)
     return W == 32 ? RAD_W32_WAVES : ((V == 0 || V == kVarBlockStep) ? RAD_W16_WAVES : RAD_W16V_WAVES);
 }
 
-template <typename InT, int PREC, int W, int DPW, int V, bool KSPLIT>
+template <typename InT, int PREC, int W, int DPW, int V>
 __global__ void __launch_bounds__(512, min_waves(W, V)) k_accumulate(AccArgs a)
 {
     extern __shared__ float4 smem4[];
-    constexpr int TD = DPW;
-    const int TO = (KSPLIT ? (blockDim.x >> 6) / a.ksplit : blockDim.x >> 6) * (64 / DPW) * W;
+    constexpr bool FLEX = DPW == 0;
+    const int TD = FLEX ? a.flex.dirs : DPW;
+    const int TO = FLEX ? a.flex.blocks * W : (blockDim.x >> 6) * (64 / (FLEX ? 64 : DPW)) * W;
     const int ntiles = a.job.tiles_d * a.job.tiles_w;
     // Workgroups are handed to the 8 XCDs round-robin; renumber them so that consecutive
     // virtual ids -- the tiles of one particle split, which read the same particle chunk --
@@ -439,8 +478,7 @@ __global__ void __launch_bounds__(512, min_waves(W, V)) k_accumulate(AccArgs a)
     // partial layout [split][omega][dir]
     float4* out = reinterpret_cast<float4*>(a.part) +
                   ((int64_t)split * a.job.n_omega + (int64_t)tw * TO) * a.job.n_dir + td * TD;
-    accumulate_range<InT, PREC, W, DPW, V, KSPLIT>(a.job, td, tw, p_begin, p_end, a.chunk, a.ksplit, out, a.job.n_dir,
-                                                   smem4);
+    accumulate_range<InT, PREC, W, DPW, V>(a.job, td, tw, p_begin, p_end, a.chunk, a.flex, out, a.job.n_dir, smem4);
 }
 
 // Persistent batched accumulate: block r processes segments [wg_seg_begin[r], wg_seg_begin[r+1]),
@@ -463,8 +501,8 @@ __global__ void __launch_bounds__(512, min_waves(W, V)) k_accumulate_batch(const
         const int tw = sg.tile / j.tiles_d;
         float4* out = reinterpret_cast<float4*>(seg_part) + (int64_t)s * TO * TD;
         const int64_t p_begin = j.i_begin + sg.c_begin * kChunk, p_cut = j.i_begin + sg.c_end * kChunk;
-        accumulate_range<InT, PREC, W, DPW, V, false>(j, td, tw, p_begin, p_cut < j.i_end ? p_cut : j.i_end, kChunk, 1,
-                                                      out, TD, smem4);
+        accumulate_range<InT, PREC, W, DPW, V>(j, td, tw, p_begin, p_cut < j.i_end ? p_cut : j.i_end, kChunk,
+                                               FlexShape{}, out, TD, smem4);
     }
 }
 
@@ -493,13 +531,11 @@ template <typename InT, int PREC, int W, int DPW, int V>
 hipError_t launch_acc_t(const AccArgs& a, const LaunchShape& s, int n_blocks, hipStream_t st,
                         hipEvent_t ev_start, hipEvent_t ev_stop)
 {
-    auto kern = a.ksplit > 1 ? k_accumulate<InT, PREC, W, DPW, V, true> : k_accumulate<InT, PREC, W, DPW, V, false>;
-    // the chunk's arrays, then (ksplit > 1) the accumulators of half the groups
-    const size_t half = (size_t)(a.ksplit / 2) * s.waves * 64 * s.w_per_lane * sizeof(float4);
-    const size_t lds = std::max(acc_lds_bytes(s), half);
-    const int threads = 64 * s.waves * a.ksplit;
-    static std::atomic<size_t> lds_allowed[2][kMaxDevices] = {};   // per instantiation and device
-    const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed[a.ksplit > 1]);
+    auto kern = k_accumulate<InT, PREC, W, DPW, V>;
+    const size_t lds = DPW == 0 ? flex_lds_bytes(a.flex, W, a.chunk) : acc_lds_bytes(s);
+    const int threads = 64 * (DPW == 0 ? a.flex.waves * a.flex.groups : s.waves);
+    static std::atomic<size_t> lds_allowed[kMaxDevices] = {};   // per instantiation and device
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed);
     if (e != hipSuccess) return e;
     if (ev_start || ev_stop) {
         AccArgs arg = a;
@@ -538,6 +574,21 @@ template <typename InT, int PREC, typename A>
 hipError_t dispatch_shape(const A& a, const LaunchShape& s, int n_blocks, hipStream_t st, hipEvent_t ev0,
                           hipEvent_t ev1)
 {
+    if constexpr (std::is_same<A, AccArgs>::value) {
+        if (a.flex.groups > 0) {
+#define RAD_FLEX_CASE(WW, VV)                                                                         \
+    if (s.w_per_lane == WW && s.variant == VV) return launch_acc_t<InT, PREC, WW, 0, VV>(a, s, n_blocks, st, ev0, ev1);
+            RAD_FLEX_CASE(32, 0)
+            RAD_FLEX_CASE(16, 0)
+            RAD_FLEX_CASE(16, 1)
+            RAD_FLEX_CASE(16, 2)
+            RAD_FLEX_CASE(16, 3)
+            RAD_FLEX_CASE(16, 4)
+            RAD_FLEX_CASE(16, 6)
+#undef RAD_FLEX_CASE
+            return hipErrorInvalidValue;
+        }
+    }
 #define RAD_SHAPE_CASE(WW, DD, VV)                                                    \
     if (s.w_per_lane == WW && s.dir_per_wave == DD && s.variant == VV) {              \
         if constexpr (std::is_same<A, AccArgs>::value)                                \

@@ -41,6 +41,16 @@ constexpr int kVarBlockStep = 4;  // piecewise-uniform list: frequency walk with
 // Frequencies per block of a piecewise-uniform list (= frequencies per lane of the variants).
 constexpr int kBlockW = 16;
 
+// Lanes of the accumulate kernel's flexible build (groups = 0: the fixed builds).
+constexpr int kFlexChunk = 128;   // particles staged at most
+struct FlexShape {
+    int32_t dirs, blocks;         // tile: directions x blocks of W frequencies
+    int32_t slots;                // sets of lanes of a wave that take particles in turn (power of two)
+    int32_t groups;               // sets of waves that do (power of two)
+    int32_t waves;                // waves of a group: slots * dirs * blocks <= 64 * waves
+    int32_t block_stride;         // floats of one block's weights in the F table (>= W)
+};
+
 // Arguments of the per-grid accumulate kernel: block b handles tile b % ntiles of split
 // b / ntiles, i.e. particles [split * per_split, +per_split) of the job, `chunk` at a time.
 struct AccArgs {
@@ -48,8 +58,8 @@ struct AccArgs {
     float* part;            // [splits][n_omega][n_dir][4] per-workgroup partial sums
     int32_t splits;
     int64_t per_split;
-    int32_t chunk;          // at most kChunk
-    int32_t ksplit;         // groups of waves that share a chunk's particles (1, 2, 4, 8)
+    int32_t chunk;          // at most kChunk (flexible build: kFlexChunk)
+    FlexShape flex;
 };
 
 // Arguments of the matrix-core accumulate kernel: frequencies [k0, k0 + n_sub) of the job's grid,
@@ -118,6 +128,15 @@ inline size_t acc_lds_bytes(const LaunchShape& s)
 
 // Limits the FP32 sums of a batcher's segments to `chunks` chunks of kChunk particles.
 void batcher_limit_segments(rad_batcher* b, int64_t chunks);
+
+// LDS of the flexible build: a chunk's arrays, then the accumulators of half the groups.
+inline size_t flex_lds_bytes(const FlexShape& f, int w, int chunk)
+{
+    const size_t arrays = (size_t)chunk * f.dirs * 24 + kFlexChunk * (11 * 8 + 8) +
+                          (size_t)chunk * f.blocks * f.block_stride * 4;
+    const size_t half = (size_t)(f.groups / 2) * f.waves * 64 * w * 16;
+    return arrays > half ? arrays : half;
+}
 
 // Sets the calling thread's message returned by rad_last_error().
 void set_last_error(const char* msg);

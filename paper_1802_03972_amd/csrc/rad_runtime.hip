@@ -231,6 +231,8 @@ struct GridPart {
     int k0 = 0, n = 0;        // frequencies [k0, k0 + n)
     bool matrix = false;      // matrix-core kernel (k0 and all below: the general one)
     rad_tile tile{};          // general kernel's launch shape
+    rad::FlexShape flex{};    // its flexible build for few directions (groups = 0: not used)
+    int flex_chunk = 0;       // and the most particles it stages at a time
     int rg = 0, fgroups = 0;  // matrix kernel: row groups per wave, frequency groups, and
     int head = 0;             // the first frequencies that it sums apart
 };
@@ -243,6 +245,7 @@ struct rad_grid {
     double C = 0;
     int cus = 0;
     rad_tile tile{};
+    bool tile_set = false;     // by rad_set_tile
     double* d_dirs9 = nullptr;
     double* d_omega = nullptr;
     float2* d_gtab = nullptr;
@@ -294,17 +297,24 @@ LaunchShape shape_of(const rad_tile& t, int variant = 0)
     return LaunchShape{t.w_per_lane, t.dir_per_wave, t.waves, variant};
 }
 
-int tiles_of(const rad_grid* g, const GridPart& p)
+int tiles_d_of(const rad_grid* g, const GridPart& p)
 {
-    const int to = rad::tile_omegas(shape_of(p.tile));
-    return (g->n_dir + p.tile.dir_per_wave - 1) / p.tile.dir_per_wave * ((p.n + to - 1) / to);
+    return p.flex.groups ? 1 : (g->n_dir + p.tile.dir_per_wave - 1) / p.tile.dir_per_wave;
 }
+int tiles_w_of(const GridPart& p)
+{
+    const int to = p.flex.groups ? p.flex.blocks * p.tile.w_per_lane : rad::tile_omegas(shape_of(p.tile));
+    return (p.n + to - 1) / to;
+}
+int tiles_of(const rad_grid* g, const GridPart& p) { return tiles_d_of(g, p) * tiles_w_of(p); }
+constexpr int kFlexResident = 2;   // workgroups of the flexible build per CU (by its LDS)
 // Particle splits that run together, rounded down: one more than fits would run alone, after
 // all the others.
 int max_splits(const rad_grid* g, const GridPart& p)
 {
     const int64_t per_split = p.matrix ? (int64_t)g->n_dir * p.fgroups : tiles_of(g, p);
-    const int64_t fit = (int64_t)g->cus * (p.matrix ? rad::mx_resident_waves(p.rg) : p.tile.wg_per_cu);
+    const int64_t fit = (int64_t)g->cus * (p.matrix ? rad::mx_resident_waves(p.rg)
+                                           : p.flex.groups ? kFlexResident : p.tile.wg_per_cu);
     return (int)std::max<int64_t>(1, fit / per_split);
 }
 size_t split_bytes(const rad_grid* g, const GridPart& p) { return (size_t)p.n * g->n_dir * 4 * sizeof(float); }
@@ -360,6 +370,57 @@ rad_tile default_tile(int n_dir, int n_omega, int variant = 0, double* cost_out 
     return best;
 }
 
+int floor_pow2(int x)
+{
+    int p = 1;
+    while (2 * p <= x) p *= 2;
+    return p;
+}
+
+// The flexible build's lanes for a grid of few directions: all directions x some blocks, up to
+// eight waves (four of the kernels with three or two waves per SIMD), particles in turn in what
+// is left of a wave and of the workgroup, and as many particles at a time as let two workgroups
+// share a CU's LDS.  The blocks per tile are those of the least cost (default_tile's scale):
+// idle lanes, the geometry that every tile computes, and the barriers of chunks in which a
+// wave gets only a few particles, as the weights of many blocks leave LDS for few.  Blocks'
+// weights are 20 floats apart where the lanes that read together span several blocks (16 would
+// put them in the same banks).
+void flex_shape(GridPart& p, int n_dir, int variant, double* cost_out)
+{
+    const bool walk = variant == 0 || variant == rad::kVarBlockStep, table = !(variant & rad::kVarShape3);
+    const int max_waves = walk ? 8 : 4;
+    const int nb = (p.n + 15) / 16;
+    double best = 0.0;
+    for (int blocks = std::min(nb, 64 * max_waves / n_dir); blocks >= 1; --blocks) {
+        rad::FlexShape f{};
+        f.dirs = n_dir;
+        f.blocks = blocks;
+        const int pairs = f.dirs * f.blocks;
+        f.waves = (pairs + 63) / 64;
+        f.slots = pairs <= 32 ? floor_pow2(64 / pairs) : 1;
+        f.groups = floor_pow2(max_waves / f.waves);
+        f.block_stride = table ? (n_dir < 8 ? 20 : 16) : 0;
+        const int per_particle = f.dirs * 24 + f.blocks * f.block_stride * 4;
+        const int fit = std::min(rad::kFlexChunk, (78 * 1024 - rad::kFlexChunk * 96) / per_particle);
+        if (fit < 1) continue;
+        while (f.groups > 1 && f.groups * f.slots > fit) f.groups /= 2;
+        while (f.slots > fit) f.slots /= 2;
+        const int rounds = fit / (f.groups * f.slots);     // of all slots and groups in a chunk
+        // waves beyond a multiple of four share two of the four SIMDs
+        const int wg_waves = f.waves * f.groups;
+        const double uneven = (wg_waves + 3) / 4 * 4.0 / wg_waves;
+        const double cost = (double)((nb + blocks - 1) / blocks) *
+                            (f.waves * (walk ? 480.0 : 830.0) / f.slots * (1.0 + 1.0 / rounds) * uneven + n_dir * 9.4 +
+                             (table ? blocks * 6.4 : 0.0));
+        if (best > 0.0 && cost >= best) continue;
+        best = cost;
+        p.flex = f;
+        p.flex_chunk = rounds * f.groups * f.slots;
+    }
+    p.tile = rad_tile{16, 16, 1, 1};
+    if (cost_out) *cost_out = best;
+}
+
 // Row groups per wave and frequency groups of the matrix kernel for n frequencies, and its cost
 // on default_tile's scale: per 16 particles 510 cycles for the columns and 560 for each row
 // group, 450 per 64 particles for the geometry.
@@ -370,6 +431,30 @@ double matrix_shape(int n_dir, int n, int* rg, int* fgroups)
     *rg = (groups + *fgroups - 1) / *fgroups;
     const double rate = *rg == 1 ? 1.0 : *rg == 2 ? 0.94 : 0.88;
     return (double)n_dir * *fgroups * ((510.0 + 560.0 * *rg) / 16.0 + 7.0) / rate;
+}
+
+// The general kernel's build and shape for a grid's first n frequencies: below kFewDirections
+// directions the fixed builds' tiles (16 and more) are mostly empty, and the flexible build is
+// used where it costs less.  Push with fold, fixed tiles and flexible: 30000 x 1 x 1000 114 and
+// 39 us, 100000 x 2 x 241 112 and 40, 30000 x 2 x 241 of an explicit list 68 and 26, 30000 x 5 x
+// 241 48 and 30, cubic cells 66 and 34, 30000 x 8 x 40 29 and 21; 30000 x 15 x 300 is faster in
+// fixed tiles (61 and 66).
+constexpr int kFewDirections = 16;
+void general_part(GridPart& p, const rad_grid* g, int n, double* cost)
+{
+    double fixed = 0.0, flex = 0.0;
+    p.n = n;
+    p.tile = default_tile(g->n_dir, n, g->variant, &fixed);
+    if (g->n_dir < kFewDirections) {
+        GridPart f;
+        f.n = n;
+        flex_shape(f, g->n_dir, g->variant, &flex);
+        if (flex < fixed) {
+            p = f;
+            fixed = flex;
+        }
+    }
+    if (cost) *cost = fixed;
 }
 
 // Which kernel accumulates which frequencies.  The matrix kernel takes the frequencies over
@@ -389,9 +474,9 @@ void plan_parts(rad_grid* g)
     mx.n = g->n_omega - mx.k0;
     if (g->variant == 0 && g->precision == RAD_PHASE_F64 && mx.n >= 16 && g->const_k0 < g->n_omega) {
         double all_cost = 0.0, lo_cost = 0.0;
-        (void)default_tile(g->n_dir, g->n_omega, 0, &all_cost);
-        lo.n = mx.k0;
-        if (lo.n > 0) lo.tile = default_tile(g->n_dir, lo.n, 0, &lo_cost);
+        GridPart any;
+        general_part(any, g, g->n_omega, &all_cost);
+        if (mx.k0 > 0) general_part(lo, g, mx.k0, &lo_cost);
         const double mx_cost = matrix_shape(g->n_dir, mx.n, &mx.rg, &mx.fgroups);
         if (lo_cost + mx_cost < 0.9 * all_cost) {
             if (lo.n > 0) g->parts.push_back(lo);
@@ -400,8 +485,12 @@ void plan_parts(rad_grid* g)
         }
     }
     GridPart all;
-    all.n = g->n_omega;
-    all.tile = g->tile;
+    general_part(all, g, g->n_omega, nullptr);
+    if (g->tile_set || !all.flex.groups) {
+        all = GridPart{};
+        all.n = g->n_omega;
+        all.tile = g->tile;
+    }
     g->parts.push_back(all);
 }
 
@@ -528,8 +617,9 @@ void fill_job(rad::Job& j, const rad_grid* g, const rad_particles* p, double t0,
 //
 // From target_splits full chunks on there is one split for each workgroup that the tile asks
 // for, all of the same length to one particle, in chunks of one length.  A smaller push has
-// fewer chunks than that: the idle waves first share the chunks' particles (ksplit, up to
-// eight waves a workgroup), then the splits get shorter, down to kMinPerSplit particles.
+// fewer chunks than that: the idle waves first share the chunks' particles (groups of the
+// flexible build, up to eight waves a workgroup), then the splits get shorter, down to
+// kMinPerSplit particles.
 // 1024 particles x 16 x 64 points 19.0 -> 8.2 us (128 workgroups of 8 waves instead of 32 of
 // one), 2000 x 2 x 241 of an explicit list 22.6 -> 10.7; 50000 x 128 x 256 of a block-stepped
 // list, 391 particles a split instead of 13 chunks in 121 of 128 splits, 380 -> 355.
@@ -543,22 +633,32 @@ int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, const Grid
         const int64_t i1 = std::min(total, i0 + per_launch_cap);
         const int64_t n = i1 - i0;
         int64_t per = (n + target_splits - 1) / target_splits;
-        int ksplit = 1;
+        int64_t most = rad::kChunk, step = 1;   // particles of a chunk: at most, and a multiple of
+        a.flex = part.flex;
         if (part.matrix) {
             per = std::max<int64_t>(32, (per + 15) / 16 * 16);
+        } else if (part.flex.groups) {
+            step = part.flex.slots * part.flex.groups;
+            most = part.flex_chunk;
+            per = std::max(per, step);
         } else if (per <= rad::kChunk) {
+            int groups = 1;
             per = rad::kChunk;
             auto fits = [&](int64_t p, int k) { return (n + p - 1) / p * k <= target_splits; };
-            while (2 * ksplit * part.tile.waves <= kMaxWaves && fits(per, 2 * ksplit)) ksplit *= 2;
-            while (per > kMinPerSplit && fits(per / 2, ksplit)) per /= 2;
+            while (2 * groups * part.tile.waves <= kMaxWaves && fits(per, 2 * groups)) groups *= 2;
+            while (per > kMinPerSplit && fits(per / 2, groups)) per /= 2;
+            if (groups > 1) {
+                const LaunchShape ls = shape_of(part.tile);
+                a.flex = rad::FlexShape{rad::tile_dirs(ls), rad::tile_omegas(ls) / ls.w_per_lane, 1, groups, ls.waves,
+                                        ls.w_per_lane};
+            }
         }
-        const int64_t chunks = (per + rad::kChunk - 1) / rad::kChunk;
+        const int64_t chunks = (per + most - 1) / most;
         a.job.i_begin = i0;
         a.job.i_end = i1;
         a.splits = (int32_t)((n + per - 1) / per);
         a.per_split = per;
-        a.chunk = (int32_t)((per + chunks - 1) / chunks);
-        a.ksplit = ksplit;
+        a.chunk = (int32_t)(((per + chunks - 1) / chunks + step - 1) / step * step);
         if (int rc = fn()) return rc;
     }
     return RAD_OK;
@@ -599,9 +699,9 @@ void part_job(rad::Job& j, const rad_grid* g, const GridPart& part, const rad_pa
 {
     fill_job(j, g, p, t0, n_per_step, part.matrix ? g->tile : part.tile);
     if (part.matrix) return;
-    const int to = rad::tile_omegas(shape_of(part.tile));
     j.n_omega = part.n;
-    j.tiles_w = (part.n + to - 1) / to;
+    j.tiles_d = tiles_d_of(g, part);
+    j.tiles_w = tiles_w_of(part);
 }
 
 // Work marked on one stream is ordered before later work on another by an event; work on
@@ -1121,11 +1221,14 @@ int rad_set_tile(rad_grid* g, const rad_tile* t)
         return fail(RAD_ERR_INVALID_ARG, "grids with a frequency list or a 3-D shape need w_per_lane = 16");
     DeviceGuard dg(g->device);
     const rad_tile old = g->tile;
+    const bool old_set = g->tile_set;
     g->tile = *t;
+    g->tile_set = true;
     plan_parts(g);
     rc = ensure_partials(g);
     if (rc) {
         g->tile = old;
+        g->tile_set = old_set;
         plan_parts(g);
     }
     return rc;

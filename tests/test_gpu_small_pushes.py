@@ -72,3 +72,33 @@ def test_variants(rad, shape, kind, dtype):
 def test_default_launch_shapes(rad, nx, ny, n_omega, shape, kind):
     om = {"uniform": None, "log": np.geomspace(1e15, 1e19, n_omega), "blocks": block_log_omegas(1e15, 1e19, n_omega)}
     check(rad, 1200, nx, ny, n_omega, shape=shape, omegas=om[kind])
+
+
+# fewer than 16 directions: the flexible build's pairs, slots, groups and frequency tiles
+@pytest.mark.parametrize("n", [1, 3, 37, 1000, 6000])
+@pytest.mark.parametrize("nx,ny,n_omega", [(1, 1, 5), (1, 1, 64), (1, 1, 1000), (2, 1, 241), (3, 1, 17), (5, 1, 130),
+                                           (7, 1, 300), (8, 1, 40), (3, 5, 100), (3, 5, 700)])
+def test_few_directions(rad, n, nx, ny, n_omega):
+    check(rad, n, nx, ny, n_omega)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape,kind", [("cic3d", "uniform"), ("cic", "log"), ("tsc", "blocks"), ("cic3d", "log"),
+                                        ("cic3d", "blocks"), ("gauss", "uniform")])
+@pytest.mark.parametrize("nx,n_omega", [(1, 300), (2, 40), (3, 77), (13, 150)])
+def test_few_directions_variants(rad, nx, n_omega, shape, kind, dtype):
+    om = {"uniform": None, "log": np.geomspace(1e15, 1e19, n_omega), "blocks": block_log_omegas(1e15, 1e19, n_omega)}
+    check(rad, 500, nx, 1, n_omega, shape=shape, dtype=dtype, omegas=om[kind], steps=3)
+
+
+def test_few_directions_all_fp32(rad):
+    """The FP32 study mode through the flexible build equals the fixed tiles' result."""
+    w = SINGLE.scaled(n_particles=300, n_steps=1, nx_dir=3, ny_dir=1, n_omega=90, seed=92, omega_max=1e15)
+    dev = to_device(w.steps(), "f32")
+    out = []
+    for tile in (None, dict(w_per_lane=16, dir_per_wave=16, waves=2, wg_per_cu=2)):
+        g = rad.Grid(w.directions(), 0.0, w.domega, 90, shape="cic", shape_len=1e-7, dt=w.dt, precision=rad.ALL_F32,
+                     tile=tile)
+        g.push_step(0.0, dev)
+        out.append(g.spectrum())
+    assert np.allclose(out[0], out[1], rtol=1e-4, atol=1e-6 * out[1].max())
