@@ -237,9 +237,11 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
             auto weights = [&](int q, float (&Fv)[4]) {
                 if constexpr (SHAPE3) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {   // F^2 = N + (N^2 - N) g(n, omega) (Eq. 12)
-                        Fv[u] = __builtin_amdgcn_sqrtf(fmaxf(fmaf(NN1, gl[4 * q + u], Nm), 0.f));
-                    }
+                    // F^2 = N + (N^2 - N) g(n, omega) (Eq. 12).  It is at least N^2; the absolute
+                    // value (an operand modifier, no instruction) keeps the rounding of N^2 - N
+                    // from a negative argument where N^2 < 6e-8 N.
+                    for (int u = 0; u < 4; ++u)
+                        Fv[u] = __builtin_amdgcn_sqrtf(fabsf(fmaf(NN1, gl[4 * q + u], Nm)));
                 } else {
                     const float4 F4 = fq[q];
                     Fv[0] = F4.x; Fv[1] = F4.y; Fv[2] = F4.z; Fv[3] = F4.w;
