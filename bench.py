@@ -756,7 +756,10 @@ def bench_precision(args) -> dict:
         avg_ms = prof["accumulate_ms"] / max(1, prof["launches"])
         out_modes[name] = {"updates_per_s_kernel": prof["updates"] / (prof["accumulate_ms"] * 1e-3),
                            "accumulate_ms": prof["accumulate_ms"], "launches": int(prof["launches"]),
-                           "roofline": alu_roofline(prof["updates"] / max(1, prof["launches"]), avg_ms, "k_accumulate",
+                           # a Gaussian far past its underflow: the FP64-phase grid's terms run on the
+                           # matrix cores, against which the FP32 vector peak is no bound
+                           "roofline": alu_roofline(prof["updates"] / max(1, prof["launches"]), avg_ms,
+                                                    "k_accumulate_mx" if name == "fp64_phase" else "k_accumulate",
                                                     fold_ms_per_launch=round(prof["fold_ms"] / max(1, prof["launches"]), 4))}
     cpu = None
     if use_oracle:

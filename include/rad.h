@@ -203,7 +203,10 @@ const char* rad_last_error(void);
  *   wg_per_cu  : workgroups per compute unit in one launch (1..16): a push is cut into
  *                CUs * wg_per_cu / tiles particle splits (the hardware runs as many of
  *                them at once as registers and LDS allow)
- * rad_set_tile validates and applies it to later pushes. */
+ * rad_set_tile validates and applies it to later pushes.  Without it, grids of fewer than
+ * 16 directions use lanes laid out for them; and on uniform grids the frequencies over which
+ * the shape factor is one constant (a point shape; a Gaussian past its underflow) go to a
+ * matrix-core kernel, which has no launch shape, wherever that costs less. */
 typedef struct rad_tile {
     int32_t w_per_lane;
     int32_t dir_per_wave;

@@ -31,8 +31,8 @@ namespace {
 // frequencies.  Up to kStepGroup steps of one push are summed in FP32 registers before one
 // read-modify-write of the FP64 integrals, so a multi-step push moves 64 B per particle and
 // grid point per group instead of per step (the main path likewise sums hundreds of
-// particles in FP32 per partial).  W = 8 (rather than 16) keeps the kernel at 162 VGPRs,
-// three waves per SIMD.
+// particles in FP32 per partial).  W = 8 (rather than 16) lets the kernel fit four
+// waves per SIMD.
 // ---------------------------------------------------------------------------------------
 constexpr int kStepGroup = 128;
 constexpr int kTrackW = 8;
