@@ -13,27 +13,39 @@
 // * Factors.  Each is sin or cos of an FP64 phase, reduced to [0, 1) revolutions before it
 //   leaves FP64 (cos as sin a quarter revolution on); nothing is walked.  The columns carry
 //   F A in FP32.
-// * FP32 product on bf16 matrix cores.  Each FP32 factor is split into three bf16 parts whose
-//   sum it is (8 + 8 + 8 bits, the exponent range of FP32), and the six products of parts down
-//   to 2^-16 of the largest are accumulated in FP32; the ones left out are below 2^-24.  The FP32
-//   matrix instructions take 16 cycles for 64 terms and add to the VALU's time; the bf16 ones
-//   take 3.75 cycles of it and run beside the rest.
+// * FP32 product on f16 matrix cores.  Each FP32 factor is split into two f16 parts (11 + 11
+//   bits and their signs), and the products of parts low high, high low and high high are
+//   summed in FP32.  The columns are held to below 1 by a power of two for each 64 particles
+//   and polarization, so that every magnitude fits f16.  The FP32 matrix instructions take 16
+//   cycles for 64 terms and add to the VALU's time; the f16 ones take 3.75 cycles of it and run
+//   beside the rest.
+// * Sums.  A matrix instruction works in passes of 8 products, and within a pass it cuts every
+//   product toward zero at 2^-24 of the largest term, the accumulator included: added to a
+//   long sum, each product would lose a part of itself that grows with the sum (measured: 16
+//   times the general kernel's error where the sums cancel, and a shrink of the order of 1e-5
+//   where they are coherent).  So each 16 particles' products are summed from zero, the small
+//   ones first, and the VALU adds the result to the FP32 sums, one rounding for 16
+//   particles.  The accumulator itself is cut toward minus infinity; the columns change sign
+//   from one 64 particles to the next, which turns that into noise.  Error of S against FP64
+//   per frequency, rms, here and in the general kernel: 16384 particles x 32 steps 1.7e-7 and
+//   3.2e-7, x 256 steps with strongly cancelling sums 2.9e-6 and 1.4e-5, 60000 x 4 coherent
+//   terms 8e-8 and 1.1e-7, identical particles 1.7e-7 and 3.6e-6.
 // * A wave owns one direction and RG x 256 frequencies, and shares nothing with other waves:
 //   64 particles at a time, each lane computes one particle's geometry (FP64, as in the general
-//   kernel) into the wave's own LDS, then four steps of 16 particles.  Consecutive waves take
+//   kernel) into the wave's own LDS, then four steps of 16 particles.  A row group's
+//   matrix products run while the VALU forms the next one's rows.  Consecutive waves take
 //   consecutive directions, so that their 16-byte partial sums fill lines.
 // * Head.  A wide grid's Gaussian differs from its constant at the first frequency or two only.
 //   Up to kMxHead of them are summed apart, each lane over its particles (weight, FP64 phase and
 //   two complex multiply-adds per particle and frequency, kept in LDS), and replace the
-//   matrix product's values there: as a launch of the general kernel over a block of 16
-//   the first of 1024 frequencies cost 570 us beside the 3430 of the others; this way 3250 us
-//   for all (16384 particles x 32 steps x 64 directions).
-// * Bound by the VALU: per 16 particles about 510 cycles for the columns and 320 for each 256
-//   frequencies' rows, half of it the splits, plus 20 for each of the 12 matrix instructions.
-//   200000 particles x 64 directions: 512 frequencies 9.6e12 terms/s, 1024 frequencies 1.1e13;
-//   128 x 256 7.6e12; the general kernel's walk 4.3e12 to 5.3e12.  With four row groups two
-//   waves per SIMD are enough (more, of fewer rows, recompute the columns: 7.6e12 and 9.7e12
-//   with one and two row groups on 1024 frequencies).
+//   matrix product's values there: a launch of the general kernel over a block of 16 for
+//   the first of 1024 frequencies costs 570 us (16384 particles x 32 steps x 64 directions),
+//   nearly a quarter of the 2430 for all of them this way.
+// * Bound by the VALU: per 16 particles about 400 cycles for the columns and, for each 256
+//   frequencies, 240 for the rows, 90 for the sums and 20 for each of the 6 matrix
+//   instructions.  200000 particles x 64 directions: 512 frequencies 1.2e13 terms/s (550 us),
+//   768 1.3e13, 1024 1.4e13; 128 x 256 8.8e12; the general kernel's walk 4.3e12 to 5.3e12.  Two
+//   waves per SIMD are enough (with three, two row groups spill: 570 us).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -47,33 +59,51 @@ namespace rad {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMxThreads = 256;
-constexpr int kMxParts = 3;
-
 // A particle as the matrix loop needs it: tau / (2 pi) and F A in the two polarizations.
 struct __align__(16) MxParticle {
     double ph;
     float a1, a2;
 };
 
-// Two FP32 values as three bf16 pairs (packed, first value in the low half) that add up to them.
-__device__ __forceinline__ void split_pair(float v0, float v1, uint32_t (&out)[kMxParts])
+// Two FP32 values as pairs of f16 parts (packed, first value in the low half), high + low.
+__device__ __forceinline__ void split_pair(float v0, float v1, uint32_t& hi, uint32_t& lo)
 {
-#pragma unroll
-    for (int p = 0; p < kMxParts; ++p) {
-        const f32x2 v = {v0, v1};
-        const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-        out[p] = b;
-        if (p + 1 < kMxParts) {
-            v0 -= __builtin_bit_cast(float, b << 16);
-            v1 -= __builtin_bit_cast(float, b & 0xffff0000u);
-        }
-    }
+    const f16x2 h = __builtin_convertvector((f32x2{v0, v1}), f16x2);
+    const f32x2 r = {v0 - static_cast<float>(h.x), v1 - static_cast<float>(h.y)};
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
+}
+
+// The largest of 64 lanes' values, in a scalar register.
+template <int CTRL>
+__device__ __forceinline__ uint32_t max_with(uint32_t v)
+{
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+    return o > v ? o : v;
+}
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    v = max_with<0x111>(v);                                 // row_shr 1, 2, 4, 8: of each 16 lanes
+    v = max_with<0x112>(v);
+    v = max_with<0x114>(v);
+    v = max_with<0x118>(v);
+    v = max_with<0x142>(v);                                 // row_bcast 15 and 31: across rows
+    v = max_with<0x143>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The power of two just above |a| of all lanes, held to 2^+-126.
+__device__ __forceinline__ int wave_exponent(float a)
+{
+    const int e = (int)(wave_max(__builtin_bit_cast(uint32_t, a) & 0x7fffffffu) >> 23) - 126;
+    return e < -126 ? -126 : e > 126 ? 126 : e;
 }
 
 // sin of 2 pi (om ph + quarter), the phase reduced in FP64.
@@ -90,7 +120,7 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr int mx_waves(int RG) { return RG == 1 ? 4 : RG == 2 ? 3 : 2; }
+constexpr int mx_waves(int RG) { return RG == 1 ? 4 : 2; }
 
 template <typename InT, int RG>
 __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxArgs a)
@@ -138,8 +168,10 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
         for (int c = 0; c < 10; ++c) f[c] = gload(static_cast<const InT*>(j.f[c]), i);
     };
     if (p_begin < p_end) load(p_begin);
+    float turn = 1.f;                                      // sign of these 64 particles' columns
     for (int64_t p0 = p_begin; p0 < p_end; p0 += 64) {
         const int cnt = p_end - p0 < 64 ? (int)(p_end - p0) : 64;
+        float up[2];                                       // what undoes the columns' sign and scale
         {
             const int64_t i = p0 + lane < p_end ? p0 + lane : p_end - 1;
             const double t = step_time(j, i);
@@ -153,8 +185,14 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
             const bool ok = lane < cnt;
             MxParticle e;
             e.ph = ok ? ph : 0.0;
-            e.a1 = ok ? F * geo.x : 0.f;
-            e.a2 = ok ? F * geo.y : 0.f;
+            e.a1 = ok ? turn * (F * geo.x) : 0.f;
+            e.a2 = ok ? turn * (F * geo.y) : 0.f;
+            const int x1 = wave_exponent(e.a1), x2 = wave_exponent(e.a2);
+            e.a1 = ldexpf(e.a1, -x1);
+            e.a2 = ldexpf(e.a2, -x2);
+            up[0] = ldexpf(turn, x1);
+            up[1] = ldexpf(turn, x2);
+            turn = -turn;
             for (int k = 0; k < head; ++k) {
                 const float g0 = gload(reinterpret_cast<const float*>(j.gtab), 2 * (int64_t)k);
                 const float g1 = gload(reinterpret_cast<const float*>(j.gtab), 2 * (int64_t)k + 1);
@@ -176,46 +214,47 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
         wave_lds_sync();
         for (int s = 0; s < cnt; s += 16) {
             const MxParticle* e = buf + s + 8 * half;      // this half wave's 8 of 16 particles
-            uint32_t col[2][kMxParts][4];
+            uint32_t col[2][2][4];                         // [polarization][high, low]
 #pragma unroll
             for (int i = 0; i < 8; i += 2) {
                 const MxParticle e0 = e[i], e1 = e[i + 1];
                 const float c0 = phase_sin(om_col, e0.ph, quarter_col), c1 = phase_sin(om_col, e1.ph, quarter_col);
-                uint32_t w[kMxParts];
-                split_pair(e0.a1 * c0, e1.a1 * c1, w);
-#pragma unroll
-                for (int p = 0; p < kMxParts; ++p) col[0][p][i / 2] = w[p];
-                split_pair(e0.a2 * c0, e1.a2 * c1, w);
-#pragma unroll
-                for (int p = 0; p < kMxParts; ++p) col[1][p][i / 2] = w[p];
+                split_pair(e0.a1 * c0, e1.a1 * c1, col[0][0][i / 2], col[0][1][i / 2]);
+                split_pair(e0.a2 * c0, e1.a2 * c1, col[1][0][i / 2], col[1][1][i / 2]);
             }
+            f32x16 sum[2];
+            auto add = [&](int g) {
+#pragma unroll
+                for (int pol = 0; pol < 2; ++pol) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[g][pol][i] = fmaf(sum[pol][i], up[pol], acc[g][pol][i]);
+                }
+            };
 #pragma unroll
             for (int g = 0; g < RG; ++g) {
-                uint32_t row[kMxParts][4];
+                uint32_t row[2][4];
 #pragma unroll
-                for (int i = 0; i < 8; i += 2) {
-                    uint32_t w[kMxParts];
-                    split_pair(phase_sin(om_row[g], e[i].ph, quarter_row), phase_sin(om_row[g], e[i + 1].ph, quarter_row), w);
+                for (int i = 0; i < 8; i += 2)
+                    split_pair(phase_sin(om_row[g], e[i].ph, quarter_row), phase_sin(om_row[g], e[i + 1].ph, quarter_row),
+                               row[0][i / 2], row[1][i / 2]);
+                if (g > 0) add(g - 1);
+                f32x16 zero;
 #pragma unroll
-                    for (int p = 0; p < kMxParts; ++p) row[p][i / 2] = w[p];
-                }
-                // parts (row, column) with 2^-(8 (row + column)) down to 2^-16, smallest first
+                for (int i = 0; i < 16; ++i) zero[i] = 0.f;
 #pragma unroll
-                for (int sum = kMxParts - 1; sum >= 0; --sum) {
+                for (int part = 0; part < 3; ++part) {     // low high, high low, high high
 #pragma unroll
-                    for (int pr = sum; pr >= 0; --pr) {
-                        const u32x4 rw = {row[pr][0], row[pr][1], row[pr][2], row[pr][3]};
-#pragma unroll
-                        for (int pol = 0; pol < 2; ++pol) {
-                            const uint32_t(&cp)[4] = col[pol][sum - pr];
-                            const u32x4 cw = {cp[0], cp[1], cp[2], cp[3]};
-                            acc[g][pol] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, rw),
-                                                                                  __builtin_bit_cast(bf16x8, cw),
-                                                                                  acc[g][pol], 0, 0, 0);
-                        }
+                    for (int pol = 0; pol < 2; ++pol) {
+                        const uint32_t(&rp)[4] = row[part == 0];
+                        const uint32_t(&cp)[4] = col[pol][part == 1];
+                        const u32x4 rw = {rp[0], rp[1], rp[2], rp[3]}, cw = {cp[0], cp[1], cp[2], cp[3]};
+                        sum[pol] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, rw),
+                                                                          __builtin_bit_cast(f16x8, cw),
+                                                                          part == 0 ? zero : sum[pol], 0, 0, 0);
                     }
                 }
             }
+            add(RG - 1);
         }
     }
 

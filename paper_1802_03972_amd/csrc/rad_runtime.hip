@@ -422,15 +422,14 @@ void flex_shape(GridPart& p, int n_dir, int variant, double* cost_out)
 }
 
 // Row groups per wave and frequency groups of the matrix kernel for n frequencies, and its cost
-// on default_tile's scale: per 16 particles 510 cycles for the columns and 560 for each row
+// on default_tile's scale: per 16 particles 420 cycles for the columns and 480 for each row
 // group, 450 per 64 particles for the geometry.
 double matrix_shape(int n_dir, int n, int* rg, int* fgroups)
 {
     const int groups = (n + rad::kMxBlock - 1) / rad::kMxBlock;
     *fgroups = (groups + 3) / 4;
     *rg = (groups + *fgroups - 1) / *fgroups;
-    const double rate = *rg == 1 ? 1.0 : *rg == 2 ? 0.94 : 0.88;
-    return (double)n_dir * *fgroups * ((510.0 + 560.0 * *rg) / 16.0 + 7.0) / rate;
+    return (double)n_dir * *fgroups * ((420.0 + 480.0 * *rg) / 16.0 + 7.0);
 }
 
 // The general kernel's build and shape for a grid's first n frequencies: below kFewDirections
@@ -460,10 +459,9 @@ void general_part(GridPart& p, const rad_grid* g, int n, double* cost)
 // Which kernel accumulates which frequencies.  The matrix kernel takes the frequencies over
 // which the shape factor is one constant, and up to kMxHead before them; with more before
 // them the general kernel takes those, in whole blocks of 16.  It is used where its waves of
-// 256 frequencies of one direction cost less than the general kernel's tiles: from about 150
-// frequencies on, from fewer for directions that fill a tile badly (both sides at 0.9: 256
-// frequencies 0.82 ms against 1.54 for 200000 particles x 128 directions; with half of a
-// wave's 256 in the grid the two are equal).
+// 256 frequencies of one direction cost less than the general kernel's tiles: from about half
+// a wave's 256 frequencies on, from fewer for directions that fill a tile badly (256
+// frequencies 0.75 ms against 1.54 for 200000 particles x 128 directions).
 void plan_parts(rad_grid* g)
 {
     g->parts.clear();

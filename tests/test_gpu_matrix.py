@@ -2,8 +2,8 @@
 its tiles -- 16-frequency rows, groups of 256, one to four groups per wave and more than one
 frequency group, chunks of 64 and steps of 16 particles, odd numbers of directions -- against
 the FP64 oracle.  Tolerances: the spectra's gate 1e-4, and 4e-6 of the largest intensity: each
-factor of a term is a 24-bit number from a hardware sin (1.1e-7) of a phase rounded to 24 bits
-(1.9e-7 rad), so |S| is off by at most about 7e-7 of the sum of the terms' sizes and I by
+factor of a term is a 22-bit number and its sign from a hardware sin (1.1e-7) of a phase rounded to 24 bits
+(1.9e-7 rad), so |S| is off by at most about 1.1e-6 of the sum of the terms' sizes and I by
 twice that where they add up, with FP32 sums of at most 1024 particles on top (4e-7)."""
 import numpy as np
 import pytest
@@ -81,6 +81,30 @@ def test_gauss_heads(rad, first, n_omega):
 def test_steps_offsets_and_first_frequency(rad, shape):
     check(rad, 123, 3, 3, 520, shape=shape, dtype="f64", steps=5, t0=1e-12)
     check(rad, 123, 3, 3, 520, shape=shape, dtype="f64", steps=3, omega0=3e18)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("kind", ["identical", "spread", "small", "large", "still"])
+def test_sizes_of_terms(rad, kind, dtype):
+    """Terms that all add up (one particle 6000 times: the error of every value is that of one
+    term and of the sum's roundings, so the 4e-6 hold at each point and not only at the peak),
+    sizes spread over many decades within each 64 particles, and sizes far from 1."""
+    w = SINGLE.scaled(n_particles=6000, n_steps=1, nx_dir=2, ny_dir=2, n_omega=256, seed=103, in_dtype=dtype, omega_max=1e15)
+    st = w.steps()
+    rates = ("dbx", "dby", "dbz")
+    if kind == "identical":
+        st = {k: np.repeat(v[:, :1], v.shape[1], axis=1) for k, v in st.items()}
+    else:
+        scale = {"spread": np.exp(4 * np.random.default_rng(5).standard_normal(6000)), "small": 1e-12, "large": 1e12,
+                 "still": 0.0}[kind]
+        held = np.float32 if dtype == "f32" else np.float64
+        st = {k: (v * scale).astype(held).astype(np.float64) if k in rates else v for k, v in st.items()}
+    g = rad.Grid(w.directions(), 0.0, w.domega, 256, shape="point", shape_len=1e-7, dt=w.dt)
+    g.push_steps(0.0, 1, to_device(st, dtype))
+    I = g.spectrum()
+    ref = oracle.spectrum(flatten(st, w.times()), w.directions(), np.arange(256) * w.domega, "point", 1e-7, w.dt)
+    bound = ref if kind == "identical" else ref.max()
+    assert (np.abs(I - ref) <= 4e-6 * bound).all(), (np.abs(I - ref) / np.maximum(bound, 1e-300)).max()
 
 
 def test_long_push_in_several_splits(rad):
