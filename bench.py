@@ -859,7 +859,8 @@ def bench_tracked(args) -> dict:
     group = rad.Tracked.step_group()
     groups = -(-w.n_steps // group)
     points = n * w.n_dir * w.n_omega
-    bytes_per_launch = 64.0 * points * groups + 40.0 * n * w.n_steps
+    # the first group of a push after a reset writes its integrals and does not read them
+    bytes_per_launch = (64.0 * groups - 32.0) * points + 40.0 * n * w.n_steps
     hbm = bytes_per_launch / (launch_ms * 1e-3) / 1e9
     # the tracked update has no form-factor scale (weights and shape enter at read-out):
     # rotate 6 + three complex multiply-adds 12 = 18 flops in the 3-component form
