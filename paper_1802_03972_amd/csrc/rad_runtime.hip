@@ -329,6 +329,8 @@ size_t split_bytes(const rad_grid* g, const GridPart& p) { return (size_t)p.n * 
 // 30000 x 37 x 100 76 -> 68 us, x 40 x 600 391 -> 245, 20000 x 88 x 730 527 -> 313, 30000 x 88 x
 // 200 of an explicit list 451 -> 277, cubic cells 415 -> 259; the best of all tiles measured 60,
 // 233, 302, 270 and 258.
+// 200000 x 128 x 48 480 -> 434, x 80 630 -> 578, 100000 x 64 x 96 214 -> 178; where it errs it costs
+// little: 200000 x 128 x 96 622 -> 641, 100000 x 128 x 300 1077 -> 1095 (16-direction tiles 1030).
 rad_tile default_tile(int n_dir, int n_omega, int variant = 0, double* cost_out = nullptr)
 {
     // Waves per SIMD by registers (128 VGPRs for the walk kernels; 142 to 175 for the others),
