@@ -75,6 +75,12 @@ class ServerCounters(ctypes.Structure):
                 ("pool_used", ctypes.c_size_t), ("now", ctypes.c_double)]
 
 
+class DebugLaunch(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int32), ("k0", ctypes.c_int32), ("n_omega", ctypes.c_int32), ("tile", Tile),
+                ("splits", ctypes.c_int32), ("per_split", ctypes.c_int64), ("chunk", ctypes.c_int32),
+                ("weights_at", ctypes.c_int32), ("lds_bytes", ctypes.c_int32)]
+
+
 # name -> (restype, argtypes); every symbol of include/rad.h and include/rad_debug.h
 _vp = ctypes.c_void_p
 _dp = ctypes.POINTER(ctypes.c_double)
@@ -128,6 +134,8 @@ SIGNATURES = {
     "rad_tracked_push_steps": (ctypes.c_int, [_vp, ctypes.c_double, ctypes.c_int32, ctypes.POINTER(Particles), _vp]),
     "rad_tracked_step_group": (ctypes.c_int, []),
     "rad_tracked_spectrum": (ctypes.c_int, [_vp, _dp, ctypes.c_int32, ctypes.c_double, _dp, _vp]),
+    "rad_debug_plan": (ctypes.c_int, [ctypes.POINTER(GridDesc), ctypes.POINTER(Tile), ctypes.c_int32, ctypes.c_int64,
+                                      ctypes.POINTER(DebugLaunch), ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]),
     "rad_debug_trig_probe": (ctypes.c_int, [_vp, _vp, ctypes.c_int, _vp]),
 }
 

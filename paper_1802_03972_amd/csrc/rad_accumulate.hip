@@ -91,7 +91,8 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
     double* taus = reinterpret_cast<double*>(geo + (FLEX ? chunk : P) * TD);
     double* raw = taus + (FLEX ? chunk : P) * TD;                    // [11][P]
     float2* nw = reinterpret_cast<float2*>(raw + 11 * P);            // [P]: (N, N^2) in FP32
-    float* ff = reinterpret_cast<float*>(nw + P);                    // [P][row_f]
+    float* ff = FLEX ? reinterpret_cast<float*>(smem4) + flex_weights_at(TD, chunk) / 4
+                     : reinterpret_cast<float*>(nw + P);             // [P][row_f], on 16 bytes
 
     constexpr bool DIRECT = (V & kVarDirect) != 0;
     constexpr bool SHAPE3 = (V & kVarShape3) != 0;

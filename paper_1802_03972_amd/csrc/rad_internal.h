@@ -129,11 +129,16 @@ inline size_t acc_lds_bytes(const LaunchShape& s)
 // Limits the FP32 sums of a batcher's segments to `chunks` chunks of kChunk particles.
 void batcher_limit_segments(rad_batcher* b, int64_t chunks);
 
-// LDS of the flexible build: a chunk's arrays, then the accumulators of half the groups.
+// LDS of the flexible build: a chunk's arrays, then the accumulators of half the groups.  The table
+// of weights starts on 16 bytes, as it is read 16 bytes at a time (an odd chunk of an odd number of
+// directions takes 8 bytes over a multiple of 16 before it).
+__host__ __device__ inline int flex_weights_at(int dirs, int chunk)
+{
+    return (chunk * dirs * 24 + kFlexChunk * (11 * 8 + 8) + 15) / 16 * 16;
+}
 inline size_t flex_lds_bytes(const FlexShape& f, int w, int chunk)
 {
-    const size_t arrays = (size_t)chunk * f.dirs * 24 + kFlexChunk * (11 * 8 + 8) +
-                          (size_t)chunk * f.blocks * f.block_stride * 4;
+    const size_t arrays = flex_weights_at(f.dirs, chunk) + (size_t)chunk * f.blocks * f.block_stride * 4;
     const size_t half = (size_t)(f.groups / 2) * f.waves * 64 * w * 16;
     return arrays > half ? arrays : half;
 }

@@ -510,6 +510,17 @@ int validate_tile(const rad_tile& t)
     return RAD_OK;
 }
 
+// The caller's launch shape, checked, as the grid's.
+int apply_tile(rad_grid* g, const rad_tile& t)
+{
+    if (int rc = validate_tile(t)) return rc;
+    if (g->variant != 0 && t.w_per_lane != 16)
+        return fail(RAD_ERR_INVALID_ARG, "grids with a frequency list or a 3-D shape need w_per_lane = 16");
+    g->tile = t;
+    g->tile_set = true;
+    return RAD_OK;
+}
+
 int ensure_partials(rad_grid* g)
 {
     size_t bytes = 0;
@@ -925,6 +936,37 @@ int prepare_tables(const rad_grid_desc* d, bool check_shape, GridTables& tb)
     return RAD_OK;
 }
 
+// What a grid is without a device: its description, and the shape table (g, 1 - g).
+void describe_grid(rad_grid* g, const rad_grid_desc* d, const GridTables& tb, int cus, std::vector<float2>& gt)
+{
+    g->device = d->device;
+    g->n_dir = d->n_dir;
+    g->n_omega = d->n_omega;
+    g->omega0 = d->omega0;
+    g->domega = d->domega;
+    g->dt = d->dt;
+    g->shape = d->shape;
+    g->shape_len = d->shape_len;
+    g->precision = d->precision;
+    g->cus = cus;
+    g->C = tb.C;
+    g->variant = tb.variant;
+    g->domega = tb.domega;
+    g->tile = default_tile(d->n_dir, d->n_omega, g->variant);
+    g->const_k0 = d->n_omega;
+    gt.resize((size_t)d->n_omega);
+    for (int k = 0; k < d->n_omega; ++k) {
+        const double gg = is_shape3(d->shape) ? 0.0 : shape_factor(d->shape, d->shape_len, tb.om[k]);
+        gt[k] = make_float2((float)gg, (float)(1.0 - gg));
+    }
+    if (!is_shape3(d->shape)) {
+        int k = d->n_omega - 1;
+        while (k > 0 && gt[k - 1].x == gt[k].x && gt[k - 1].y == gt[k].y) --k;
+        g->const_k0 = k;
+        g->const_g = gt[d->n_omega - 1];
+    }
+}
+
 }  // namespace
 
 void rad::set_last_error(const char* msg) { t_last_error = msg ? msg : ""; }
@@ -957,34 +999,9 @@ int rad_create_grid(rad_grid** out, const rad_grid_desc* d)
     if (cus < 0) return cus;
 
     rad_grid* g = new rad_grid;
-    g->device = d->device;
-    g->n_dir = d->n_dir;
-    g->n_omega = d->n_omega;
-    g->omega0 = d->omega0;
-    g->domega = d->domega;
-    g->dt = d->dt;
-    g->shape = d->shape;
-    g->shape_len = d->shape_len;
-    g->precision = d->precision;
-    g->cus = cus;
-    g->C = tb.C;
-    g->variant = tb.variant;
-    g->domega = tb.domega;
-    g->tile = default_tile(d->n_dir, d->n_omega, g->variant);
-    g->const_k0 = d->n_omega;
-
     std::vector<double>& om = tb.om;
-    std::vector<float2> gt((size_t)d->n_omega);
-    for (int k = 0; k < d->n_omega; ++k) {
-        const double gg = is_shape3(d->shape) ? 0.0 : shape_factor(d->shape, d->shape_len, om[k]);
-        gt[k] = make_float2((float)gg, (float)(1.0 - gg));
-    }
-    if (!is_shape3(d->shape)) {
-        int k = d->n_omega - 1;
-        while (k > 0 && gt[k - 1].x == gt[k].x && gt[k - 1].y == gt[k].y) --k;
-        g->const_k0 = k;
-        g->const_g = gt[d->n_omega - 1];
-    }
+    std::vector<float2> gt;
+    describe_grid(g, d, tb, cus, gt);
     plan_parts(g);
     std::vector<float> g3;
     if (is_shape3(d->shape)) {
@@ -1215,15 +1232,11 @@ int rad_get_tile(const rad_grid* g, rad_tile* t)
 int rad_set_tile(rad_grid* g, const rad_tile* t)
 {
     if (!g || !t) return fail(RAD_ERR_INVALID_ARG, "grid and tile must be non-NULL");
-    int rc = validate_tile(*t);
-    if (rc) return rc;
-    if (g->variant != 0 && t->w_per_lane != 16)
-        return fail(RAD_ERR_INVALID_ARG, "grids with a frequency list or a 3-D shape need w_per_lane = 16");
     DeviceGuard dg(g->device);
     const rad_tile old = g->tile;
     const bool old_set = g->tile_set;
-    g->tile = *t;
-    g->tile_set = true;
+    int rc = apply_tile(g, *t);
+    if (rc) return rc;
     plan_parts(g);
     rc = ensure_partials(g);
     if (rc) {
@@ -1237,6 +1250,49 @@ int rad_set_tile(rad_grid* g, const rad_tile* t)
 }  // extern "C"
 
 #include "rad_debug.h"
+
+extern "C" int rad_debug_plan(const rad_grid_desc* d, const rad_tile* tile, int32_t cus, int64_t n_particles,
+                              rad_debug_launch* out, int32_t max_launches, int32_t* n_launches)
+{
+    if (!d || !n_launches || max_launches < 0 || (max_launches > 0 && !out) || cus < 1 || n_particles < 0)
+        return fail(RAD_ERR_INVALID_ARG, "bad plan arguments");
+    GridTables tb;
+    if (int rc = prepare_tables(d, true, tb)) return rc;
+    rad_grid g;
+    std::vector<float2> gt;
+    describe_grid(&g, d, tb, cus, gt);
+    if (tile) {
+        if (int rc = apply_tile(&g, *tile)) return rc;
+    }
+    plan_parts(&g);
+    int32_t n = 0;
+    for (const GridPart& part : g.parts) {
+        AccArgs a{};
+        for_each_launch(a, n_particles, max_splits(&g, part), part, [&]() -> int {
+            if (n < max_launches) {
+                rad_debug_launch l{};
+                l.kernel = part.matrix ? 2 : a.flex.groups ? 1 : 0;
+                l.k0 = part.k0;
+                l.n_omega = part.n;
+                l.tile = part.tile;
+                l.splits = a.splits;
+                l.per_split = a.per_split;
+                l.chunk = a.chunk;
+                if (l.kernel == 1) {
+                    l.weights_at = rad::flex_weights_at(a.flex.dirs, a.chunk);
+                    l.lds_bytes = (int32_t)rad::flex_lds_bytes(a.flex, part.tile.w_per_lane, a.chunk);
+                } else if (l.kernel == 0) {
+                    l.lds_bytes = (int32_t)rad::acc_lds_bytes(shape_of(part.tile));
+                }
+                out[n] = l;
+            }
+            ++n;
+            return RAD_OK;
+        });
+    }
+    *n_launches = n;
+    return RAD_OK;
+}
 
 extern "C" int rad_debug_trig_probe(const float* in_dev, float* out_dev, int n, void* stream)
 {
