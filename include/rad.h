@@ -159,7 +159,9 @@ int rad_push_steps(rad_grid* g, double t0, int32_t n_steps, int64_t n_particles,
  * race and give wrong results; order them on one stream.
  * Under HIP stream capture the call records no event and waits on none, so the captured
  * kernels carry no ordering against the grid's other work: capture after that work has
- * completed and replay on the stream that issues the grid's other calls. */
+ * completed and replay on the stream that issues the grid's other calls.  The grid's other
+ * calls, rad_batcher_push and rad_tracked_spectrum refuse a capturing stream with
+ * RAD_ERR_INVALID_ARG. */
 #define RAD_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 int rad_push_step_noalloc(rad_grid* g, double t, int64_t n_particles, const rad_particles* p,
                           void* stream);

@@ -715,6 +715,24 @@ void part_job(rad::Job& j, const rad_grid* g, const GridPart& part, const rad_pa
     j.tiles_w = tiles_w_of(part);
 }
 
+bool captures(hipStream_t st, hipError_t* e)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    *e = st ? hipStreamIsCapturing(st, &cap) : hipSuccess;   // the null stream cannot capture
+    return cap != hipStreamCaptureStatusNone;
+}
+
+// Calls that read or set the grid's marks, the partial-sum buffers' turn or a plan, or that wait
+// for the stream, are of no use in a graph: a replay knows nothing of the marks, and a mark made
+// in a capture is no event that later work could wait for.
+int refuse_capture(hipStream_t st, const char* call)
+{
+    hipError_t e;
+    const bool capturing = captures(st, &e);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
+    return capturing ? fail(RAD_ERR_INVALID_ARG, "%s cannot be captured (rad_push_step_noalloc can)", call) : RAD_OK;
+}
+
 // Work marked on one stream is ordered before later work on another by an event; work on
 // the stream of the mark needs none.  On a caller's own stream the event is recorded when the
 // work is issued (the stream may be gone when somebody asks).  The null stream is always
@@ -1069,6 +1087,7 @@ int rad_reset(rad_grid* g, void* stream)
 {
     if (!g) return fail(RAD_ERR_INVALID_ARG, "grid is NULL");
     DeviceGuard dg(g->device);
+    if (int rc = refuse_capture((hipStream_t)stream, "rad_reset")) return rc;
     hipStream_t st = (hipStream_t)stream;
     RAD_HIP(order_after(g->last_write, st));
     hipError_t e = rad::launch_reset(g->d_S, (int64_t)g->n_dir * g->n_omega * 4, g->d_err, st);
@@ -1086,6 +1105,7 @@ int rad_push_step(rad_grid* g, double t, int64_t n_particles, const rad_particle
     int rc = check_particles(p);
     if (rc) return rc;
     DeviceGuard dg(g->device);
+    if ((rc = refuse_capture((hipStream_t)stream, "rad_push_step"))) return rc;
     return push_range(g, t, n_particles, n_particles, p, (hipStream_t)stream);
 }
 
@@ -1099,6 +1119,7 @@ int rad_push_steps(rad_grid* g, double t0, int32_t n_steps, int64_t n_particles,
     int rc = check_particles(p);
     if (rc) return rc;
     DeviceGuard dg(g->device);
+    if ((rc = refuse_capture((hipStream_t)stream, "rad_push_steps"))) return rc;
     return push_range(g, t0, n_particles, (int64_t)n_steps * n_particles, p, (hipStream_t)stream);
 }
 
@@ -1125,9 +1146,9 @@ int rad_push_step_noalloc(rad_grid* g, double t, int64_t n_particles, const rad_
     // Under stream capture the call records no event and waits on none (a wait on an event
     // recorded outside the capture, or another stream waiting on the capture, would break
     // it): the caller orders the captured push against the grid's other work.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    RAD_HIP(hipStreamIsCapturing(st, &cap));
-    const bool capturing = cap != hipStreamCaptureStatusNone;
+    hipError_t cap_err;
+    const bool capturing = captures(st, &cap_err);
+    RAD_HIP(cap_err);
     // every fold of this grid runs in issue order: the folds below come after every fold
     // already issued (on any stream), later folds, read-outs and resets after them
     if (!capturing) RAD_HIP(order_after(g->last_write, st));
@@ -1155,6 +1176,7 @@ int rad_spectrum_device(rad_grid* g, double* I_dev, void* stream)
 {
     if (!g || !I_dev) return fail(RAD_ERR_INVALID_ARG, "grid and output must be non-NULL");
     DeviceGuard dg(g->device);
+    if (int rc = refuse_capture((hipStream_t)stream, "rad_spectrum_device")) return rc;
     hipStream_t st = (hipStream_t)stream;
     RAD_HIP(order_after(g->last_write, st));
     hipError_t e = rad::launch_finalize(g->d_S, I_dev, g->n_dir, g->n_omega, g->C, g->d_err, nullptr, st);
@@ -1169,6 +1191,7 @@ int rad_spectrum(rad_grid* g, double* I_host, void* stream)
 {
     if (!g || !I_host) return fail(RAD_ERR_INVALID_ARG, "grid and output must be non-NULL");
     DeviceGuard dg(g->device);
+    if (int rc = refuse_capture((hipStream_t)stream, "rad_spectrum")) return rc;
     return read_out(g, I_host, (size_t)g->n_dir * g->n_omega, (hipStream_t)stream, [&](double* out, int* flag_out, hipStream_t st) {
         return rad::launch_finalize(g->d_S, out, g->n_dir, g->n_omega, g->C, g->d_err, flag_out, st);
     });
@@ -1178,6 +1201,7 @@ int rad_spectrum_complex(rad_grid* g, double* S_host, void* stream)
 {
     if (!g || !S_host) return fail(RAD_ERR_INVALID_ARG, "grid and output must be non-NULL");
     DeviceGuard dg(g->device);
+    if (int rc = refuse_capture((hipStream_t)stream, "rad_spectrum_complex")) return rc;
     return read_out(g, S_host, (size_t)g->n_dir * g->n_omega * 6, (hipStream_t)stream, [&](double* out, int* flag_out, hipStream_t st) {
         return rad::launch_cartesian(g->d_S, g->d_dirs9, out, g->n_dir, g->n_omega, g->d_err, flag_out, st);
     });
@@ -1192,6 +1216,7 @@ int rad_get_state(rad_grid* g, double* state_host, void* stream)
 {
     if (!g || !state_host) return fail(RAD_ERR_INVALID_ARG, "grid and state must be non-NULL");
     DeviceGuard dg(g->device);
+    if (int rc = refuse_capture((hipStream_t)stream, "rad_get_state")) return rc;
     hipStream_t st = (hipStream_t)stream;
     RAD_HIP(order_after(g->last_write, st));
     int flag = 0;
@@ -1207,6 +1232,7 @@ int rad_set_state(rad_grid* g, const double* state_host, void* stream)
 {
     if (!g || !state_host) return fail(RAD_ERR_INVALID_ARG, "grid and state must be non-NULL");
     DeviceGuard dg(g->device);
+    if (int rc = refuse_capture((hipStream_t)stream, "rad_set_state")) return rc;
     hipStream_t st = (hipStream_t)stream;
     RAD_HIP(order_after(g->last_write, st));
     RAD_HIP(hipMemcpyAsync(g->d_S, state_host, rad_state_size(g) * sizeof(double), hipMemcpyHostToDevice, st));
@@ -1602,6 +1628,7 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
     }
     DeviceGuard dg(b->device);
     hipStream_t st = (hipStream_t)stream;
+    if (int rc = refuse_capture(st, "rad_batcher_push")) return rc;
     // earlier single-grid folds of these grids must land before the batch fold
     {
         std::vector<rad_grid*> seen;
@@ -1977,9 +2004,10 @@ namespace {
 
 int note_capture(rad_tracked* tr, hipStream_t st)
 {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    RAD_HIP(hipStreamIsCapturing(st, &cap));
-    if (cap != hipStreamCaptureStatusNone) {
+    hipError_t e;
+    const bool capturing = captures(st, &e);
+    RAD_HIP(e);
+    if (capturing) {
         tr->captured = true;
         tr->T_zero = false;
     }
@@ -2068,6 +2096,7 @@ extern "C" int rad_tracked_spectrum(rad_tracked* tr, const double* weights_host,
             return fail(RAD_ERR_INVALID_ARG, "weight %lld must be finite and >= 0", (long long)m);
     DeviceGuard dg(tr->device);
     hipStream_t st = (hipStream_t)stream;
+    if (int rc = refuse_capture(st, "rad_tracked_spectrum")) return rc;
     const bool s3 = is_shape3(shape);
     // weights, then the shape factors, as the device buffer holds them
     const size_t points = (size_t)tr->n_dir * tr->n_omega, n_g = s3 ? points : (size_t)tr->n_omega;
