@@ -205,10 +205,12 @@ const char* rad_last_error(void);
  *   wg_per_cu  : workgroups per compute unit in one launch (1..16): a push is cut into
  *                CUs * wg_per_cu / tiles particle splits (the hardware runs as many of
  *                them at once as registers and LDS allow)
- * rad_set_tile validates and applies it to later pushes.  Without it, grids of fewer than
- * 16 directions use lanes laid out for them; and on uniform grids the frequencies over which
- * the shape factor is one constant (a point shape; a Gaussian past its underflow) go to a
- * matrix-core kernel, which has no launch shape, wherever that costs less. */
+ * rad_set_tile validates it and applies it to all frequencies of later pushes.  Without it, grids
+ * of fewer than 16 directions use lanes laid out for them; and on uniform grids the
+ * frequencies over which the shape factor is one constant (a point shape; a Gaussian past its
+ * underflow) go to a matrix-core kernel, which has no launch shape, wherever that costs
+ * less.  rad_hint_tile is for shapes from a table keyed by a grid's size: it takes the place
+ * of the built-in choice of tile, and the matrix-core kernel is used as without it. */
 typedef struct rad_tile {
     int32_t w_per_lane;
     int32_t dir_per_wave;
@@ -217,6 +219,7 @@ typedef struct rad_tile {
 } rad_tile;
 int rad_get_tile(const rad_grid* g, rad_tile* t);
 int rad_set_tile(rad_grid* g, const rad_tile* t);
+int rad_hint_tile(rad_grid* g, const rad_tile* t);
 
 /* Kernel variant chosen for a grid at creation, as bits (or a negative code):
  *   1  explicit frequency list, per-term FP64 phase

@@ -78,9 +78,9 @@ class Grid:
                  device: int = 0, tile="auto", omegas=None):
         """omegas: optional explicit frequency list (any spacing); then omega0/domega are
         ignored and n_omega is its length.
-        tile: "auto" applies the autotuner's table entry for this grid shape if present
-        (else the library's heuristic), None keeps the heuristic, or a dict of launch-shape
-        fields (w_per_lane, dir_per_wave, waves, wg_per_cu)."""
+        tile: "auto" hints the autotuner's table entry for this grid shape if present (else
+        the library's heuristic), None keeps the heuristic, or a dict of launch-shape
+        fields (w_per_lane, dir_per_wave, waves, wg_per_cu) to set."""
         L = _lib.lib()
         self._dirs = np.ascontiguousarray(dirs, np.float64).reshape(-1, 3)
         self.n_dir = int(self._dirs.shape[0])
@@ -108,7 +108,7 @@ class Grid:
             from .autotune import lookup
             t = lookup(self.n_dir, self.n_omega, int(precision), variant=self.variant)
             if t is not None:
-                self.set_tile(**t)
+                self._tile(L.rad_hint_tile, t)
         elif isinstance(tile, dict):
             self.set_tile(**tile)
 
@@ -219,10 +219,14 @@ class Grid:
         return {k: getattr(t, k) for k, _ in _lib.Tile._fields_}
 
     def set_tile(self, **kw) -> None:
+        """Launch shape of later pushes, for all frequencies (fields left out stay as they are)."""
+        self._tile(_lib.lib().rad_set_tile, kw)
+
+    def _tile(self, call, kw) -> None:
         cur = self.get_tile()
         cur.update(kw)
         t = _lib.Tile(*[int(cur[k]) for k, _ in _lib.Tile._fields_])
-        _lib.check(_lib.lib().rad_set_tile(self._h, ctypes.byref(t)))
+        _lib.check(call(self._h, ctypes.byref(t)))
 
 
 class Batcher:

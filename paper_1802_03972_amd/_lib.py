@@ -102,6 +102,7 @@ SIGNATURES = {
     "rad_grid_variant": (ctypes.c_int, [_vp]),
     "rad_get_tile": (ctypes.c_int, [_vp, ctypes.POINTER(Tile)]),
     "rad_set_tile": (ctypes.c_int, [_vp, ctypes.POINTER(Tile)]),
+    "rad_hint_tile": (ctypes.c_int, [_vp, ctypes.POINTER(Tile)]),
     "rad_device_cus": (ctypes.c_int, [ctypes.c_int32]),
     "rad_profile_enable": (ctypes.c_int, [_vp, ctypes.c_int]),
     "rad_profile_read": (ctypes.c_int, [_vp, ctypes.POINTER(ProfileStats)]),

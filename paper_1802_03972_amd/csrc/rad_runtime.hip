@@ -245,7 +245,9 @@ struct rad_grid {
     double C = 0;
     int cus = 0;
     rad_tile tile{};
-    bool tile_set = false;     // by rad_set_tile
+    // Where the tile is from: the cost model, a table of measured tiles (rad_hint_tile: the general
+    // kernel's fixed tiles take it, other routes stay open) or the caller (rad_set_tile).
+    enum TileFrom { kTileDefault, kTileHint, kTileSet } tile_from = kTileDefault;
     double* d_dirs9 = nullptr;
     double* d_omega = nullptr;
     float2* d_gtab = nullptr;
@@ -463,10 +465,18 @@ void general_part(GridPart& p, const rad_grid* g, int n, double* cost)
 // them the general kernel takes those, in whole blocks of 16.  It is used where its waves of
 // 256 frequencies of one direction cost less than the general kernel's tiles: from about half
 // a wave's 256 frequencies on, from fewer for directions that fill a tile badly (256
-// frequencies 0.75 ms against 1.54 for 200000 particles x 128 directions).
+// frequencies 0.75 ms against 1.54 for 200000 particles x 128 directions).  A launch shape that the
+// caller set takes the whole grid.
 void plan_parts(rad_grid* g)
 {
     g->parts.clear();
+    if (g->tile_from == rad_grid::kTileSet) {
+        GridPart set;
+        set.n = g->n_omega;
+        set.tile = g->tile;
+        g->parts.push_back(set);
+        return;
+    }
     GridPart lo, mx;
     mx.matrix = true;
     mx.head = g->const_k0 <= rad::kMxHead ? g->const_k0 : 0;
@@ -486,7 +496,7 @@ void plan_parts(rad_grid* g)
     }
     GridPart all;
     general_part(all, g, g->n_omega, nullptr);
-    if (g->tile_set || !all.flex.groups) {
+    if (g->tile_from == rad_grid::kTileHint || !all.flex.groups) {
         all = GridPart{};
         all.n = g->n_omega;
         all.tile = g->tile;
@@ -510,14 +520,14 @@ int validate_tile(const rad_tile& t)
     return RAD_OK;
 }
 
-// The caller's launch shape, checked, as the grid's.
-int apply_tile(rad_grid* g, const rad_tile& t)
+// A launch shape, checked, as the grid's.
+int apply_tile(rad_grid* g, const rad_tile& t, rad_grid::TileFrom from)
 {
     if (int rc = validate_tile(t)) return rc;
     if (g->variant != 0 && t.w_per_lane != 16)
         return fail(RAD_ERR_INVALID_ARG, "grids with a frequency list or a 3-D shape need w_per_lane = 16");
     g->tile = t;
-    g->tile_set = true;
+    g->tile_from = from;
     return RAD_OK;
 }
 
@@ -542,6 +552,24 @@ int ensure_partials(rad_grid* g)
     }
     g->part_bytes = bytes;
     return RAD_OK;
+}
+
+int change_tile(rad_grid* g, const rad_tile* t, rad_grid::TileFrom from)
+{
+    if (!g || !t) return fail(RAD_ERR_INVALID_ARG, "grid and tile must be non-NULL");
+    DeviceGuard dg(g->device);
+    const rad_tile old = g->tile;
+    const rad_grid::TileFrom old_from = g->tile_from;
+    int rc = apply_tile(g, *t, from);
+    if (rc) return rc;
+    plan_parts(g);
+    rc = ensure_partials(g);
+    if (rc) {
+        g->tile = old;
+        g->tile_from = old_from;
+        plan_parts(g);
+    }
+    return rc;
 }
 
 void release_events(rad_grid* g)
@@ -1255,23 +1283,9 @@ int rad_get_tile(const rad_grid* g, rad_tile* t)
     return RAD_OK;
 }
 
-int rad_set_tile(rad_grid* g, const rad_tile* t)
-{
-    if (!g || !t) return fail(RAD_ERR_INVALID_ARG, "grid and tile must be non-NULL");
-    DeviceGuard dg(g->device);
-    const rad_tile old = g->tile;
-    const bool old_set = g->tile_set;
-    int rc = apply_tile(g, *t);
-    if (rc) return rc;
-    plan_parts(g);
-    rc = ensure_partials(g);
-    if (rc) {
-        g->tile = old;
-        g->tile_set = old_set;
-        plan_parts(g);
-    }
-    return rc;
-}
+int rad_set_tile(rad_grid* g, const rad_tile* t) { return change_tile(g, t, rad_grid::kTileSet); }
+
+int rad_hint_tile(rad_grid* g, const rad_tile* t) { return change_tile(g, t, rad_grid::kTileHint); }
 
 }  // extern "C"
 
@@ -1288,7 +1302,7 @@ extern "C" int rad_debug_plan(const rad_grid_desc* d, const rad_tile* tile, int3
     std::vector<float2> gt;
     describe_grid(&g, d, tb, cus, gt);
     if (tile) {
-        if (int rc = apply_tile(&g, *tile)) return rc;
+        if (int rc = apply_tile(&g, *tile, rad_grid::kTileSet)) return rc;
     }
     plan_parts(&g);
     int32_t n = 0;

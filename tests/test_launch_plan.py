@@ -44,3 +44,27 @@ def test_flexible_lds(n_dir, kind):
                 assert l.chunk <= 128 and 2 * l.lds_bytes <= 160 * 1024
     if n_dir in (7, 9, 11, 13, 15):      # the odd chunks that this is about
         assert odd > 0
+
+
+TILE = (16, 32, 4, 3)
+
+
+@pytest.mark.parametrize("shape", ["point", "gauss", "cic"])
+@pytest.mark.parametrize("n_dir,n_omega", [(1, 1000), (8, 256), (36, 100), (64, 1024), (128, 300)])
+def test_a_set_tile_takes_the_whole_grid(n_dir, n_omega, shape):
+    """A launch shape that the caller sets is the one that every push runs, for all frequencies, also
+    on grids that would otherwise go to the matrix cores in part or in whole."""
+    for n in [1000, 200000]:
+        for l in plan(n_dir, n_omega, n, shape=shape, tile=TILE):
+            assert l.kernel != MATRIX and (l.k0, l.n_omega) == (0, n_omega)
+            assert tuple(getattr(l.tile, k) for k, _ in _lib.Tile._fields_) == TILE
+    free = plan(n_dir, n_omega, 200000, shape=shape)
+    assert any(l.kernel == MATRIX for l in free) == (shape != "cic")
+
+
+def test_a_gaussian_in_two_parts_covers_every_frequency():
+    """More than four frequencies before the constant: the general kernel takes whole blocks of 16."""
+    parts = plan(16, 600, 1000, shape="gauss", omega_max=2e18)
+    assert [l.kernel for l in parts][-1] == MATRIX and len(parts) == 2
+    assert parts[0].k0 == 0 and parts[0].n_omega == parts[1].k0 and parts[1].k0 % 16 == 0
+    assert parts[1].k0 + parts[1].n_omega == 600
