@@ -333,7 +333,10 @@ typedef struct rad_server_counters {
 } rad_server_counters;
 
 /* Start a server with its own scheduler thread, copy and compute streams (default
- * priority) and a device chunk pool of hbm_budget bytes on cfg->device. */
+ * priority) and a device chunk pool of hbm_budget bytes on cfg->device.  Beside the pool it
+ * holds the partial sums of its launches: 16 B for each point of a tile x (workgroups of a
+ * launch + 16 max_batch) with graphs, x (workgroups + tiles of the batch) without, and a
+ * quarter on top (0.3 GiB for 16 x 512-point tiles, 1024 workgroups and max_batch 64). */
 int rad_server_create(rad_server** out, const rad_server_config* cfg);
 
 /* Queue one chunk: n particles of one time step t of `grid`, given in HOST memory (SoA,

@@ -126,8 +126,9 @@ inline size_t acc_lds_bytes(const LaunchShape& s)
     return kChunk * td * 16 + kChunk * td * 8 + 11 * kChunk * 8 + kChunk * 8 + kChunk * to * 4;
 }
 
-// Limits the FP32 sums of a batcher's segments to `chunks` chunks of kChunk particles.
-void batcher_limit_segments(rad_batcher* b, int64_t chunks);
+// Limits the FP32 sums in registers of a batcher's launches to `chunks` chunks of kChunk particles
+// (0, as created: to a workgroup's range).
+void batcher_limit_sums(rad_batcher* b, int chunks);
 
 // LDS of the flexible build: a chunk's arrays, then the accumulators of half the groups.  The table
 // of weights starts on 16 bytes, as it is read 16 bytes at a time (an odd chunk of an odd number of
@@ -159,11 +160,12 @@ int mx_resident_waves(int rg);
 // count = 4 * grid points (FP32 values per split); part is 16-byte aligned.
 hipError_t launch_fold(const float* part, double* S, int splits, int64_t count, hipStream_t st,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// sum_chunks: chunks of a sum in registers at most (0: whole segments).
 hipError_t launch_accumulate_batch(const Job* items, const int32_t* wg_seg_begin, const BatchSeg* segs,
-                                   float* seg_part, int dtype, int precision,
+                                   float* seg_part, int sum_chunks, int dtype, int precision,
                                    const LaunchShape& s, int n_blocks, hipStream_t st);
 // Kernel attributes only (no launch), so that a later stream capture records launches only.
-hipError_t prepare_accumulate_batch(int dtype, int precision, const LaunchShape& s);
+hipError_t prepare_accumulate_batch(int sum_chunks, int dtype, int precision, const LaunchShape& s);
 // n_jobs is read on the device (from n_jobs_dev) so that a captured graph can be replayed
 // with different plans; the grid is sized for max_jobs.
 hipError_t launch_fold_batch(const int32_t* n_jobs_dev, const FoldJob* jobs, int max_jobs,

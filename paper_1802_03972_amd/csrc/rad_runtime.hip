@@ -1423,9 +1423,9 @@ struct rad_batcher {
     // graph mode: captured [plan upload -> accumulate -> fold] per launch configuration
     bool tile_set = false;       // launch shape of the batched kernel (else the built-in
     rad_tile tile{};             // heuristic for the first item's grid shape)
-    // A segment sums at most this many chunks in FP32 (the range's end and the tile's are the
-    // other limits).  The server sets it.
-    int64_t seg_chunks = INT64_MAX;
+    // A sum in registers covers at most this many chunks (0: no limit but the end of a workgroup's
+    // range and of a tile).  The server sets it.
+    int sum_chunks = 0;
     bool graph_mode = false;
     hipStream_t cap_stream = nullptr;
     std::vector<BatchGraph> graphs;
@@ -1491,12 +1491,7 @@ struct LaunchPlan {
     std::vector<int32_t> seg_list;
 };
 
-// Segments a workgroup may have in graph mode, whose buffers have a fixed size: one for each
-// tile it meets, or, with a limit on their length, this many on average (longer launches get
-// longer segments then).
-constexpr int kGraphSegsPerRange = 8;
-
-void build_plan(const std::vector<ItemInfo>& items, int64_t L0, int64_t L1, int R, int64_t max_seg, LaunchPlan& pl)
+void build_plan(const std::vector<ItemInfo>& items, int64_t L0, int64_t L1, int R, LaunchPlan& pl)
 {
     pl = LaunchPlan{};
     const int64_t I = L1 - L0;
@@ -1512,7 +1507,7 @@ void build_plan(const std::vector<ItemInfo>& items, int64_t L0, int64_t L1, int 
             const int64_t local = pos - in.iter_begin;
             const int64_t tile = local / in.chunks;
             const int64_t c0 = local % in.chunks;
-            const int64_t seg_end = std::min(pos + std::min(end - pos, max_seg), in.iter_begin + (tile + 1) * in.chunks);
+            const int64_t seg_end = std::min(end, in.iter_begin + (tile + 1) * in.chunks);
             pl.segs.push_back(rad::BatchSeg{(int32_t)it, (int32_t)tile, c0, c0 + (seg_end - pos)});
             pos = seg_end;
         }
@@ -1586,7 +1581,7 @@ extern "C" int rad_batcher_destroy(rad_batcher* b)
     return RAD_OK;
 }
 
-void rad::batcher_limit_segments(rad_batcher* b, int64_t chunks) { b->seg_chunks = chunks; }
+void rad::batcher_limit_sums(rad_batcher* b, int chunks) { b->sum_chunks = chunks; }
 
 extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int32_t n_items, void* stream)
 {
@@ -1665,26 +1660,19 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
     for (int64_t L0 = 0; L0 < I; L0 += per_launch) {
         const int64_t L1 = std::min(I, L0 + per_launch);
         const int R = (int)std::min<int64_t>(R_target, L1 - L0);
-        int64_t max_seg = b->seg_chunks;
-        if (b->graph_mode && max_seg < INT64_MAX) {
-            const int64_t most = (int64_t)R_target * (kGraphSegsPerRange - 1);
-            max_seg = std::max(max_seg, (L1 - L0 + most - 1) / most);
-        }
         LaunchPlan pl;
-        build_plan(info, L0, L1, R, max_seg, pl);
+        build_plan(info, L0, L1, R, pl);
         // Plan layout: header {n_items, n_segs, n_jobs, R} | items | wg_seg_begin | segs |
         // jobs | seg_list.  In graph mode the capacities (and the launched grid) are fixed
         // so one captured graph serves every plan that fits.
         const int R_fixed = R_target;
-        const size_t jobs_cap_g = (size_t)R_fixed + 16 * (size_t)b->max_items;
-        const size_t segs_cap_g = (b->seg_chunks < INT64_MAX ? (size_t)kGraphSegsPerRange * R_fixed : (size_t)R_fixed) +
-                                   16 * (size_t)b->max_items;
-        bool use_graph = b->graph_mode && pl.segs.size() <= segs_cap_g && pl.jobs.size() <= jobs_cap_g &&
+        const size_t segs_cap_g = (size_t)R_fixed + 16 * (size_t)b->max_items;
+        bool use_graph = b->graph_mode && pl.segs.size() <= segs_cap_g && pl.jobs.size() <= segs_cap_g &&
                          pl.seg_list.size() <= segs_cap_g;
         const int R_launch = use_graph ? R_fixed : R;
         const size_t items_cap = use_graph ? (size_t)b->max_items : info.size();
         const size_t segs_cap = use_graph ? segs_cap_g : pl.segs.size();
-        const size_t jobs_cap = use_graph ? jobs_cap_g : pl.jobs.size();
+        const size_t jobs_cap = use_graph ? segs_cap_g : pl.jobs.size();
         const size_t list_cap = use_graph ? segs_cap_g : pl.seg_list.size();
         const size_t o_hdr = 0;
         const size_t o_items = 16;
@@ -1751,13 +1739,13 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
             if (!exec) {
                 // capture [plan upload -> persistent accumulate -> fold] on the batcher's own stream
                 hipGraph_t graph = nullptr;
-                hipError_t e = rad::prepare_accumulate_batch(dtype, g0->precision, ls);
+                hipError_t e = rad::prepare_accumulate_batch(b->sum_chunks, dtype, g0->precision, ls);
                 if (e == hipSuccess) e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
                 if (e == hipSuccess) {
                     hipError_t e1 = hipMemcpyAsync(sl.dev, sl.host, bytes, hipMemcpyHostToDevice, b->cap_stream);
                     if (e1 == hipSuccess)
-                        e1 = rad::launch_accumulate_batch(d_items, d_wsb, d_segs, b->seg_part, dtype, g0->precision,
-                                                          ls, R_launch, b->cap_stream);
+                        e1 = rad::launch_accumulate_batch(d_items, d_wsb, d_segs, b->seg_part, b->sum_chunks, dtype,
+                                                          g0->precision, ls, R_launch, b->cap_stream);
                     if (e1 == hipSuccess)
                         e1 = rad::launch_fold_batch(d_njobs, d_jobs, (int)jobs_cap, d_list, b->seg_part, TD, TO,
                                                     b->cap_stream);
@@ -1808,8 +1796,8 @@ extern "C" int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int
         } else {
             RAD_HIP(hipMemcpyAsync(sl.dev, sl.host, bytes, hipMemcpyHostToDevice, st));
             if (b->profiling) RAD_HIP(hipEventRecord(e0, st));
-            hipError_t e = rad::launch_accumulate_batch(d_items, d_wsb, d_segs, b->seg_part, dtype, g0->precision,
-                                                        ls, R_launch, st);
+            hipError_t e = rad::launch_accumulate_batch(d_items, d_wsb, d_segs, b->seg_part, b->sum_chunks, dtype,
+                                                        g0->precision, ls, R_launch, st);
             if (e != hipSuccess) return hip_fail(e, "batch accumulate launch");
             if (b->profiling) {
                 RAD_HIP(hipEventRecord(e1, st));

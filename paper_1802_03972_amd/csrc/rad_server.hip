@@ -96,12 +96,14 @@ private:
 };
 
 // Chunks fall into batches by when they arrive, so a range of a batched launch may hold a whole
-// chunk of a small bunch or a part of many.  Its FP32 sum, whose rounding grows with its
-// length, is cut at 512 particles: with sums of a few thousand the error of a served spectrum
-// against FP64 was 0.4e-6 to 1.3e-6 from run to run, with the cut at most 0.8e-6, at the same
-// rate (10.0 ms for 16 chunks of 8 bunches on 128 x 512 points; the extra partial tiles are
-// folded at 5 TB/s).
-constexpr int64_t kSegmentChunks = 512 / rad::kChunk;
+// chunk of a small bunch or a part of many, and the same chunks may be summed in other ranges the
+// next time.  A sum in registers, whose FP32 rounding grows with its length, is cut at 512
+// particles: with sums of a few thousand the error of a served spectrum against FP64 was 0.4e-6 to
+// 1.3e-6 from run to run, with the cut 0.6e-6 to 0.9e-6, in the same time (10.1 ms for 16 chunks
+// of 8 bunches on 128 x 512 points).  A plain batch's ranges are the same for the same items, and
+// there the cut costs more than it gives: error 1.5e-6 to 2.1e-6 uncut and 1.1e-6 to 1.2e-6 cut,
+// 3.27 against 3.34 ms (twelve bunches of 1e3 to 5e5 particles on 64 x 256 points).
+constexpr int kSumChunks = 512 / rad::kChunk;
 
 constexpr size_t kFieldAlign = 256;
 
@@ -301,7 +303,7 @@ int rad_server_create(rad_server** out, const rad_server_config* cfg)
         return srv_fail(RAD_ERR_INVALID_ARG, "bad device");
     }
     int rc = rad_batcher_create(&s->batcher, cfg->device, cfg->max_batch);
-    if (rc == RAD_OK) rad::batcher_limit_segments(s->batcher, kSegmentChunks);
+    if (rc == RAD_OK) rad::batcher_limit_sums(s->batcher, kSumChunks);
     if (rc == RAD_OK && cfg->use_graph) rc = rad_batcher_set_graph(s->batcher, 1);
     if (rc != RAD_OK) {
         if (s->batcher) rad_batcher_destroy(s->batcher);
