@@ -292,6 +292,7 @@ namespace {
 // longer pushes are cut into several launches, each folded into the FP64 accumulator).
 constexpr int64_t kMaxPerWorkgroup = 32768;
 constexpr int64_t kMinPerSplit = 8;
+constexpr int64_t kFewSplits = 32;
 constexpr int kMaxWaves = 8;     // of one workgroup
 
 LaunchShape shape_of(const rad_tile& t, int variant = 0)
@@ -651,14 +652,17 @@ void fill_job(rad::Job& j, const rad_grid* g, const rad_particles* p, double t0,
 
 // Cuts particles [0, total) into launches of at most target_splits particle splits of at most
 // kMaxPerWorkgroup particles each, and sets a's particle range and its split into workgroups
-// for each launch before calling fn() (which returns a status code).  `waves` is the waves of
-// a workgroup that covers the tile once.
+// for each launch before calling fn() (which returns a status code).
 //
 // From target_splits full chunks on there is one split for each workgroup that the tile asks
 // for, all of the same length to one particle, in chunks of one length.  A smaller push has
 // fewer chunks than that: the idle waves first share the chunks' particles (groups of the
 // flexible build, up to eight waves a workgroup), then the splits get shorter, down to
-// kMinPerSplit particles.
+// kMinPerSplit particles.  The flexible build of few directions has its groups already; where
+// they are one, its splits may be shorter than that as long as there are only kFewSplits of
+// them (each is a partial tile to write and to fold: 15 x 540 points, 1500 particles 34 us in
+// splits of 3 and 22 in splits of 8; 256 particles 20.6 and 15; 16 particles 11.9 in splits of
+// 1 and 13.2 of 8).
 // 1024 particles x 16 x 64 points 19.0 -> 8.2 us (128 workgroups of 8 waves instead of 32 of
 // one), 2000 x 2 x 241 of an explicit list 22.6 -> 10.7; 50000 x 128 x 256 of a block-stepped
 // list, 391 particles a split instead of 13 chunks in 121 of 128 splits, 380 -> 355.
@@ -679,7 +683,7 @@ int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, const Grid
         } else if (part.flex.groups) {
             step = part.flex.slots * part.flex.groups;
             most = part.flex_chunk;
-            per = std::max(per, step);
+            per = std::max({per, step, std::min(kMinPerSplit, (n + kFewSplits - 1) / kFewSplits)});
         } else if (per <= rad::kChunk) {
             int groups = 1;
             per = rad::kChunk;

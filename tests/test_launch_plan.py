@@ -68,3 +68,15 @@ def test_a_gaussian_in_two_parts_covers_every_frequency():
     assert [l.kernel for l in parts][-1] == MATRIX and len(parts) == 2
     assert parts[0].k0 == 0 and parts[0].n_omega == parts[1].k0 and parts[1].k0 % 16 == 0
     assert parts[1].k0 + parts[1].n_omega == 600
+
+
+@pytest.mark.parametrize("kind", ["uniform", "log", "blocks"])
+@pytest.mark.parametrize("n_dir,n_omega", [(1, 1000), (3, 100), (5, 800), (7, 1024), (11, 300), (11, 529), (15, 540), (15, 1000),
+                                           (16, 64), (37, 100), (128, 256)])
+def test_small_pushes_do_not_split_to_single_particles(n_dir, n_omega, kind):
+    """Each split writes a whole partial tile that the fold reads: at least 8 particles each once there
+    are 32 splits, and all particles are in one of them."""
+    for n in [1, 2, 15, 31, 32, 33, 64, 255, 256, 257, 600, 1500, 4000, 4097, 50000]:
+        for l in plan(n_dir, n_omega, n, kind):
+            assert (l.splits - 1) * l.per_split < n <= l.splits * l.per_split
+            assert l.splits <= 32 or l.per_split >= 8, (n, l.splits, l.per_split)
