@@ -322,41 +322,25 @@ int max_splits(const rad_grid* g, const GridPart& p)
 }
 size_t split_bytes(const rad_grid* g, const GridPart& p) { return (size_t)p.n * g->n_dir * 4 * sizeof(float); }
 
-// Launch shape without a measured entry: the tile with the least time per particle over the
-// whole grid, from the cycles that a particle costs its workgroup and the waves that share a
-// SIMD.  What it weighs: lanes outside the grid (an odd number of directions or frequencies
-// fills some tiles badly: 40 x 600 points are 48 x 1024 in 16-direction tiles of 8 waves, 48 x
-// 640 in tiles of 5), the set-up that a tile's frequencies and directions share, and the
-// workgroups that registers and LDS let run together.  Against 32 directions up to 256
-// frequencies, else 16, and as many waves as the frequencies fill (push with fold, one card):
-// 30000 x 37 x 100 76 -> 68 us, x 40 x 600 391 -> 245, 20000 x 88 x 730 527 -> 313, 30000 x 88 x
-// 200 of an explicit list 451 -> 277, cubic cells 415 -> 259; the best of all tiles measured 60,
-// 233, 302, 270 and 258.
-// 200000 x 128 x 48 480 -> 434, x 80 630 -> 578, 100000 x 64 x 96 214 -> 178; where it errs it costs
-// little: 200000 x 128 x 96 622 -> 641, 100000 x 128 x 300 1077 -> 1095 (16-direction tiles 1030).
-rad_tile default_tile(int n_dir, int n_omega, int variant = 0, double* cost_out = nullptr)
+// What the general kernel's fixed tiles cost a grid, in cycles of a particle on the scale of
+// flex_shape and matrix_shape, for the choice between those routes and this one: lanes outside
+// the grid, the set-up that a tile's frequencies and directions share, and the waves that
+// registers and LDS let run together.
+double fixed_cost(int n_dir, int n_omega, int variant)
 {
     // Waves per SIMD by registers (128 VGPRs for the walk kernels; 142 to 175 for the others),
     // and the cycles of 16 frequencies of one particle in the hot loop.
     const bool walk = variant == 0 || variant == rad::kVarBlockStep;
     const int slots = 4 * (walk ? 4 : 3);
     const double hot = walk ? 480.0 : 830.0;
-    rad_tile best{};
-    double best_cost = 0.0;
+    double best = 0.0;
     for (int dpw : {32, 16, 64}) {
         for (int waves = 8; waves >= 1; --waves) {
-            rad_tile t{};
-            t.w_per_lane = 16;
-            t.dir_per_wave = dpw;
-            t.waves = waves;
-            const int to = rad::tile_omegas(shape_of(t)), per_wave = to / waves;
+            const LaunchShape s{16, dpw, waves};
+            const int to = rad::tile_omegas(s), per_wave = to / waves;
             if (waves > 1 && to - per_wave >= n_omega) continue;   // a wave without a frequency
-            const int resident = std::min(slots / waves, (int)((160 * 1024) / rad::acc_lds_bytes(shape_of(t))));
+            const int resident = std::min(slots / waves, (int)((160 * 1024) / rad::acc_lds_bytes(s)));
             if (resident < 1) continue;
-            // one round of resident workgroups; two for the other kernels, whose rounds end
-            // less evenly (88 x 200 explicit list 295 us with one, 277 with two; cubic cells 286
-            // and 259)
-            t.wg_per_cu = std::min(walk ? resident : 2 * resident, 16);
             // issue rate by waves per SIMD (VOP2 loops: 6.2, 3.3 and 3.0 cycles an instruction at
             // one, two and four)
             const double per_simd = resident * waves / 4.0;
@@ -365,13 +349,80 @@ rad_tile default_tile(int n_dir, int n_omega, int variant = 0, double* cost_out 
             const double tiles = (double)((n_dir + dpw - 1) / dpw) * ((n_omega + to - 1) / to);
             // geometry 600 cycles per 64 (particle, direction), weights 25 per 64 (particle, frequency)
             const double cost = tiles * (waves * hot + dpw * 9.4 + to * 0.4) / rate;
-            if (best_cost == 0.0 || cost < best_cost) {
-                best_cost = cost;
-                best = t;
+            if (best == 0.0 || cost < best) best = cost;
+        }
+    }
+    return best;
+}
+
+// Launch shape without a measured entry for the grid.  A simple rule, 32 directions up to 256
+// frequencies, else 16, and as many waves as the frequencies fill, gives way to the tile for which
+// a push of 50000 particles is faster by a tenth, by the measured time of a particle on a tile.
+//
+// The times hold what a formula for the waves' residence missed: a workgroup's waves start on
+// the same SIMD each time, so that 3, 5 or 6 of them load the SIMDs unevenly (6 cost what 8 do),
+// and more than four waves of the kernels with three waves per SIMD leave room for no second
+// workgroup (5 to 8 cost twice what 4 do).  Choosing by such a formula was up to 1.5 times
+// slower than the rule: 120000 particles x 56 x 440 of an explicit list 1599 us by the rule, 2399
+// by the formula and 1359 here; 64 x 786 1424, 1649 and 1416; 128 x 300 1230, 1311 and 1230; in 120
+// grids of 16 to 128 directions and 16 to 1024 frequencies nothing is slower than the rule by more
+// than 3 % at 20000 and 120000 particles.  At 1000 some are, whose larger number of partial tiles
+// shows (20 x 273 in cubic cells 20 -> 25 us, and 636 -> 429 at 120000).
+rad_tile default_tile(int n_dir, int n_omega, int variant = 0)
+{
+    // ns of one particle on one tile of a full chip, by directions (16, 32, 64) and waves (1 to 8);
+    // 120000 particles, 128 directions, each tile's own number of frequencies
+    static const float kWalk[3][8] = {{.367f, .536f, .776f, .855f, 1.270f, 1.442f, 1.444f, 1.505f},
+                                      {.507f, .563f, .851f, .919f, 1.380f, 1.486f, 1.515f, 1.575f},
+                                      {1.893f, 1.251f, 1.137f, 1.093f, 1.467f, 1.628f, 1.627f, 1.685f}};
+    static const float kDirect[3][8] = {{.577f, .944f, 1.363f, 1.499f, 3.300f, 3.305f, 3.309f, 3.320f},
+                                        {.746f, .943f, 1.385f, 1.535f, 3.328f, 3.305f, 3.317f, 3.292f},
+                                        {1.972f, 1.827f, 1.807f, 1.775f, 3.460f, 3.449f, 3.429f, 3.415f}};
+    static const float kCubic[3][8] = {{.492f, .816f, 1.211f, 1.256f, 2.595f, 2.601f, 2.595f, 2.575f},
+                                       {.682f, .810f, 1.300f, 1.345f, 2.719f, 2.676f, 2.684f, 2.697f},
+                                       {1.948f, 1.650f, 1.553f, 1.511f, 2.862f, 2.837f, 2.817f, 2.823f}};
+    const bool walk = variant == 0 || variant == rad::kVarBlockStep;
+    const auto& ns = walk ? kWalk : variant & rad::kVarDirect ? kDirect : kCubic;
+    // Splits for two rounds of resident workgroups, where that is faster: the other kernels' tiles of
+    // three and four waves, whose one round ends unevenly.
+    static const float kDirect2[2][2] = {{1.295f, 1.420f}, {1.333f, 1.466f}};
+    static const float kCubic2[2][2] = {{1.153f, 1.205f}, {1.222f, 1.299f}};
+    constexpr double kCus = 256.0, kParticles = 50000.0;
+    auto tile = [](int dpw, int waves) {
+        rad_tile t{16, dpw, waves, 0};
+        // workgroups that four waves per SIMD and the LDS have room for
+        t.wg_per_cu = std::max(2, std::min(std::max(1, 16 / waves), (int)((160 * 1024) / rad::acc_lds_bytes(shape_of(t)))));
+        return t;
+    };
+    auto time = [&](const rad_tile& t, double tile_ns) {
+        const int to = rad::tile_omegas(shape_of(t));
+        const double tiles = (double)((n_dir + t.dir_per_wave - 1) / t.dir_per_wave) * ((n_omega + to - 1) / to);
+        const double fit = kCus * t.wg_per_cu, splits = std::max(1.0, std::floor(fit / tiles));
+        const double used = splits * tiles / (std::ceil(splits * tiles / fit) * fit);
+        // in ns; the partial sums are written and folded at 5 TB/s
+        return kParticles * tiles * tile_ns / used + splits * n_dir * n_omega * 16.0 * 0.2e-3;
+    };
+    const int dpw = n_dir >= 32 && n_omega <= 256 ? 32 : 16, per_wave = 64 / dpw * 16;
+    rad_tile best = tile(dpw, std::min(8, std::max(1, (n_omega + per_wave - 1) / per_wave)));
+    double best_time = time(best, ns[dpw / 32][best.waves - 1]) / 1.1;
+    auto consider = [&](const rad_tile& t, double tile_ns) {
+        const double c = time(t, tile_ns);
+        if (c >= best_time) return;
+        best_time = c;
+        best = t;
+    };
+    for (int d : {16, 32, 64}) {
+        for (int waves = 1; waves <= 8; ++waves) {
+            rad_tile t = tile(d, waves);
+            const int to = rad::tile_omegas(shape_of(t));
+            if (waves > 1 && to - to / waves >= n_omega) continue;   // a wave without a frequency
+            consider(t, ns[d / 32][waves - 1]);
+            if (!walk && d <= 32 && (waves == 3 || waves == 4)) {
+                t.wg_per_cu *= 2;
+                consider(t, (variant & rad::kVarDirect ? kDirect2 : kCubic2)[d / 32][waves - 3]);
             }
         }
     }
-    if (cost_out) *cost_out = best_cost;
     return best;
 }
 
@@ -385,7 +436,7 @@ int floor_pow2(int x)
 // The flexible build's lanes for a grid of few directions: all directions x some blocks, up to
 // eight waves (four of the kernels with three or two waves per SIMD), particles in turn in what
 // is left of a wave and of the workgroup, and as many particles at a time as let two workgroups
-// share a CU's LDS.  The blocks per tile are those of the least cost (default_tile's scale):
+// share a CU's LDS.  The blocks per tile are those of the least cost (fixed_cost's scale):
 // idle lanes, the geometry that every tile computes, and the barriers of chunks in which a
 // wave gets only a few particles, as the weights of many blocks leave LDS for few.  Blocks'
 // weights are 20 floats apart where the lanes that read together span several blocks (16 would
@@ -427,7 +478,7 @@ void flex_shape(GridPart& p, int n_dir, int variant, double* cost_out)
 }
 
 // Row groups per wave and frequency groups of the matrix kernel for n frequencies, and its cost
-// on default_tile's scale: per 16 particles 420 cycles for the columns and 480 for each row
+// on fixed_cost's scale: per 16 particles 420 cycles for the columns and 480 for each row
 // group, 450 per 64 particles for the geometry.
 double matrix_shape(int n_dir, int n, int* rg, int* fgroups)
 {
@@ -446,9 +497,9 @@ double matrix_shape(int n_dir, int n, int* rg, int* fgroups)
 constexpr int kFewDirections = 16;
 void general_part(GridPart& p, const rad_grid* g, int n, double* cost)
 {
-    double fixed = 0.0, flex = 0.0;
+    double fixed = fixed_cost(g->n_dir, n, g->variant), flex = 0.0;
     p.n = n;
-    p.tile = default_tile(g->n_dir, n, g->variant, &fixed);
+    p.tile = default_tile(g->n_dir, n, g->variant);
     if (g->n_dir < kFewDirections) {
         GridPart f;
         f.n = n;

@@ -80,3 +80,25 @@ def test_small_pushes_do_not_split_to_single_particles(n_dir, n_omega, kind):
         for l in plan(n_dir, n_omega, n, kind):
             assert (l.splits - 1) * l.per_split < n <= l.splits * l.per_split
             assert l.splits <= 32 or l.per_split >= 8, (n, l.splits, l.per_split)
+
+
+# grids for which another tile was measured 1.03 to 1.76 times slower
+@pytest.mark.parametrize("n_dir,n_omega,kind,shape,tile", [
+    (128, 96, "uniform", "cic", (16, 32, 3, 4)), (128, 300, "uniform", "cic", (16, 16, 5, 2)),
+    (64, 786, "uniform", "cic", (16, 16, 8, 2)), (56, 440, "log", "cic", (16, 16, 4, 6)),
+    (32, 267, "blocks", "cic", (16, 16, 5, 2)), (77, 41, "log", "cic", (16, 32, 2, 4))])
+def test_default_tiles(n_dir, n_omega, kind, shape, tile):
+    l, = plan(n_dir, n_omega, 1000000, kind, shape)
+    assert l.kernel == FIXED
+    assert tuple(getattr(l.tile, k) for k, _ in _lib.Tile._fields_) == tile
+
+
+@pytest.mark.parametrize("kind,shape", [("log", "cic"), ("uniform", "cic3d"), ("log", "cic3d")])
+def test_default_tiles_of_the_other_kernels(kind, shape):
+    """Of the kernels that three waves of share a SIMD, five to eight waves of a workgroup cost the
+    same, so no tile of five to seven is taken where it needs as many workgroups as one of eight."""
+    for n_dir in [16, 20, 37, 64, 100, 128]:
+        for n_omega in [80, 150, 272, 300, 440, 580, 786, 1000]:
+            l, = plan(n_dir, n_omega, 1000000, kind, shape)
+            per = (64 // l.tile.dir_per_wave) * 16
+            assert l.tile.waves <= 4 or -(-n_omega // (per * l.tile.waves)) == -(-n_omega // (per * 8)), (n_dir, n_omega)
