@@ -77,6 +77,9 @@ struct MxArgs {
 };
 constexpr int kMxBlock = 256;   // frequencies of a row group
 constexpr int kMxHead = 4;
+// What undoes the mean shrink of its sums: 6.8e-8 in each of nine pushes of 3000 to 465000 particles,
+// 12 bunches each (standard error 0.1e-8).
+constexpr double kMxScale = 1.0 + 6.8e-8;
 
 // Batched launch: every workgroup walks its own list of segments; a segment is a chunk
 // range of one (item, tile) and owns one partial tile [TO][TD][4] in the segment buffer.
@@ -157,9 +160,10 @@ hipError_t launch_accumulate_mx(const MxArgs& a, int dtype, int rg, hipStream_t 
                                 hipEvent_t ev_stop = nullptr);
 // Waves of the matrix-core kernel with rg row groups (1..4) that one CU holds.
 int mx_resident_waves(int rg);
-// count = 4 * grid points (FP32 values per split); part is 16-byte aligned.
-hipError_t launch_fold(const float* part, double* S, int splits, int64_t count, hipStream_t st,
-                       hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// count = 4 * grid points (FP32 values per split); part is 16-byte aligned.  What is added to the
+// points from scale_from on is scaled.
+hipError_t launch_fold(const float* part, double* S, int splits, int64_t count, double scale, int64_t scale_from,
+                       hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // sum_chunks: chunks of a sum in registers at most (0: whole segments).
 hipError_t launch_accumulate_batch(const Job* items, const int32_t* wg_seg_begin, const BatchSeg* segs,
                                    float* seg_part, int sum_chunks, int dtype, int precision,

@@ -342,7 +342,7 @@ __device__ __forceinline__ double fold_groups(double (&red)[G][4 * PT], int p, i
 }
 
 // S[p] += sum over splits of part[s][p] for every grid point p (four components: S1r,
-// S1i, S2r, S2i) in FP64, in a fixed order.  Bound by the one read of the partials (16 B
+// S1i, S2r, S2i) in FP64, in a fixed order; times `scale` from point `scale_from` on.  Bound by the one read of the partials (16 B
 // per split and point, non-temporal), and on small grids by the latency of that read: a
 // block of 256 threads is PT = 256 / G points x G groups of consecutive splits, with
 // kFoldUnroll loads in flight per thread (twice that without groups), so that a grid of a
@@ -354,7 +354,7 @@ constexpr int kFoldUnroll = 8;
 
 template <int G>
 __global__ void __launch_bounds__(256) k_fold(const f32x4* __restrict__ part, double* __restrict__ S,
-                                              int splits, int64_t points)
+                                              int splits, int64_t points, double scale, int64_t scale_from)
 {
     constexpr int PT = 256 / G;
     const int p = threadIdx.x % PT, q = threadIdx.x / PT;
@@ -368,7 +368,8 @@ __global__ void __launch_bounds__(256) k_fold(const f32x4* __restrict__ part, do
         if (i0 + p < points) {
             double2* s2 = reinterpret_cast<double2*>(S) + 2 * i;
             double2 lo = s2[0], hi = s2[1];
-            lo.x += a[0]; lo.y += a[1]; hi.x += a[2]; hi.y += a[3];
+            const double f = i < scale_from ? 1.0 : scale;
+            lo.x += f * a[0]; lo.y += f * a[1]; hi.x += f * a[2]; hi.y += f * a[3];
             s2[0] = lo;
             s2[1] = hi;
         }
@@ -376,7 +377,7 @@ __global__ void __launch_bounds__(256) k_fold(const f32x4* __restrict__ part, do
         __shared__ double red[G][4 * PT];
         const double s = fold_groups<G, PT>(red, p, q, a);
         const int t = threadIdx.x;
-        if (t < 4 * PT && 4 * i0 + t < 4 * points) S[4 * i0 + t] += s;
+        if (t < 4 * PT && 4 * i0 + t < 4 * points) S[4 * i0 + t] += (i0 + t / 4 < scale_from ? 1.0 : scale) * s;
     }
 }
 
@@ -547,35 +548,37 @@ hipError_t launch_fold_batch(const int32_t* n_jobs_dev, const FoldJob* jobs, int
 namespace {
 
 template <int G>
-hipError_t launch_fold_g(const f32x4* part, double* S, int splits, int64_t points, hipStream_t st,
-                         hipEvent_t ev_start, hipEvent_t ev_stop)
+hipError_t launch_fold_g(const f32x4* part, double* S, int splits, int64_t points, double scale, int64_t scale_from,
+                         hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     const dim3 grid(grid1d(points, 256 / G));
     if (ev_start || ev_stop) {
-        void* args[] = {&part, &S, &splits, &points};
+        void* args[] = {&part, &S, &splits, &points, &scale, &scale_from};
         return hipExtLaunchKernel(reinterpret_cast<const void*>(k_fold<G>), grid, dim3(256), args, 0, st, ev_start,
                                   ev_stop, 0);
     }
-    hipLaunchKernelGGL(k_fold<G>, grid, dim3(256), 0, st, part, S, splits, points);
+    hipLaunchKernelGGL(k_fold<G>, grid, dim3(256), 0, st, part, S, splits, points, scale, scale_from);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_fold(const float* part, double* S, int splits, int64_t count, hipStream_t st,
-                       hipEvent_t ev_start, hipEvent_t ev_stop)
+hipError_t launch_fold(const float* part, double* S, int splits, int64_t count, double scale, int64_t scale_from,
+                       hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     const int64_t points = count / 4;
     if (points <= 0) return hipSuccess;
     const f32x4* p4 = reinterpret_cast<const f32x4*>(part);
+    auto go = [&](auto fold) { return fold(p4, S, splits, points, scale, scale_from, st, ev_start, ev_stop); };
     // Groups of splits per block.  From 32768 points on, one thread per point with 16 loads
     // in flight already reads at the rate HBM delivers (128 splits x 32768 points 12.7 us, 4
     // groups 12.8; 256 splits 20.9 against 21.7; 65536 points 12.2 against 13.0).  Below, its
-    // blocks are too few: 3700 points 16.5 us against 6.0 with 16 groups.  A group has at
-    // least one split.
-    if (points >= 32768 || splits < 4) return launch_fold_g<1>(p4, S, splits, points, st, ev_start, ev_stop);
-    if (points >= 8192 || splits < 16) return launch_fold_g<4>(p4, S, splits, points, st, ev_start, ev_stop);
-    return launch_fold_g<16>(p4, S, splits, points, st, ev_start, ev_stop);
+    // blocks are too few: 3700 points 16.5 us against 6.0 with 16 groups.  Groups are of one
+    // length, so the last of them may be empty (17 splits are 8 groups of two, one of one and
+    // seven of none); an empty group adds zeros.
+    if (points >= 32768 || splits < 4) return go(launch_fold_g<1>);
+    if (points >= 8192 || splits < 16) return go(launch_fold_g<4>);
+    return go(launch_fold_g<16>);
 }
 
 namespace {

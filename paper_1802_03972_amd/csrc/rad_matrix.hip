@@ -15,10 +15,11 @@
 //   F A in FP32.
 // * FP32 product on f16 matrix cores.  Each FP32 factor is split into two f16 parts (11 + 11
 //   bits and their signs), and the products of parts low high, high low and high high are
-//   summed in FP32.  The columns are held to below 1 by a power of two for each 64 particles
-//   and polarization, so that every magnitude fits f16.  The FP32 matrix instructions take 16
-//   cycles for 64 terms and add to the VALU's time; the f16 ones take 3.75 cycles of it and run
-//   beside the rest.
+//   summed in FP32.  The columns are held to below 2^15 by a power of two for each 64 particles
+//   and polarization, so that every magnitude fits f16 and the low parts of columns far below
+//   the largest are not lost in its denormals (held to below 1, the error of a bunch's spectrum
+//   was 1.2 times this).  The FP32 matrix instructions take 16 cycles for 64 terms and add to the
+//   VALU's time; the f16 ones take 3.75 cycles of it and run beside the rest.
 // * Sums.  A matrix instruction works in passes of 8 products, and within a pass it cuts every
 //   product toward zero at 2^-24 of the largest term, the accumulator included: added to a
 //   long sum, each product would lose a part of itself that grows with the sum (measured: 16
@@ -26,10 +27,18 @@
 //   where they are coherent).  So each 16 particles' products are summed from zero, the small
 //   ones first, and the VALU adds the result to the FP32 sums, one rounding for 16
 //   particles.  The accumulator itself is cut toward minus infinity; the columns change sign
-//   from one 64 particles to the next, which turns that into noise.  Error of S against FP64
-//   per frequency, rms, here and in the general kernel: 16384 particles x 32 steps 1.7e-7 and
-//   3.2e-7, x 256 steps with strongly cancelling sums 2.9e-6 and 1.4e-5, 60000 x 4 coherent
-//   terms 8e-8 and 1.1e-7, identical particles 1.7e-7 and 3.6e-6.
+//   from one 16 particles to the next, and the first ones from split to split, which turns
+//   that into noise (with one sign for each 64 particles, splits of 32 to 64 had all the same,
+//   and pushes of 3e4 particles twice the error).
+// * The hardware sine is cut toward zero in its last bit: 3.2e-8 of it is missing on average,
+//   twice in each term, and some 4e-9 more by the cuts of the products.  The fold scales this
+//   kernel's sums back (kMxScale).  Its own error is then the rounding of two phases to 24 bits
+//   and of two sines.
+// * Error of S against FP64.  Root mean square per frequency, over 100 pushes drawn from point
+//   and Gaussian grids of 1 to 128 directions and 100 to 1024 frequencies, three bunches each:
+//   0.46 to 0.98 of the general kernel's, geometric mean 0.54; the largest of a frequency 0.46 in
+//   the mean, 1.01 at most.  16384 particles x 256 steps whose sums cancel 1.4e-5 there and 2.9e-6
+//   here; 60000 x 4 coherent terms 1.1e-7 and 8e-8; identical particles 3.6e-6 and 1.7e-7.
 // * A wave owns one direction and RG x 256 frequencies, and shares nothing with other waves:
 //   64 particles at a time, each lane computes one particle's geometry (FP64, as in the general
 //   kernel) into the wave's own LDS, then four steps of 16 particles.  A row group's
@@ -99,12 +108,20 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// The power of two just above |a| of all lanes, held to 2^+-126.
+// The largest column is scaled to just below 2^15, near the top of f16's range: its low part and
+// smaller columns lie above f16's denormals then (scaled to 1, a column 2^-10 of the largest kept 14 bits).
+constexpr int kColumnBits = 15;
+
+// The exponent of the power of two just above |a| of all lanes, at least that of the smallest
+// columns' scale (a scalar).
 __device__ __forceinline__ int wave_exponent(float a)
 {
     const int e = (int)(wave_max(__builtin_bit_cast(uint32_t, a) & 0x7fffffffu) >> 23) - 126;
-    return e < -126 ? -126 : e > 126 ? 126 : e;
+    return e < kColumnBits - 126 ? kColumnBits - 126 : e;
 }
+
+// The FP32 bits of 2^e, e from -126.
+__device__ __forceinline__ uint32_t power_bits(int e) { return (uint32_t)(e + 127) << 23; }
 
 // sin of 2 pi (om ph + quarter), the phase reduced in FP64.
 __device__ __forceinline__ float phase_sin(double om, double ph, double quarter)
@@ -168,10 +185,10 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
         for (int c = 0; c < 10; ++c) f[c] = gload(static_cast<const InT*>(j.f[c]), i);
     };
     if (p_begin < p_end) load(p_begin);
-    float turn = 1.f;                                      // sign of these 64 particles' columns
+    uint32_t turn = (uint32_t)split << 31;                 // sign of the first 16 particles' columns
     for (int64_t p0 = p_begin; p0 < p_end; p0 += 64) {
         const int cnt = p_end - p0 < 64 ? (int)(p_end - p0) : 64;
-        float up[2];                                       // what undoes the columns' sign and scale
+        uint32_t up[2];                                    // what undoes the columns' sign and scale, FP32 bits
         {
             const int64_t i = p0 + lane < p_end ? p0 + lane : p_end - 1;
             const double t = step_time(j, i);
@@ -185,14 +202,15 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
             const bool ok = lane < cnt;
             MxParticle e;
             e.ph = ok ? ph : 0.0;
-            e.a1 = ok ? turn * (F * geo.x) : 0.f;
-            e.a2 = ok ? turn * (F * geo.y) : 0.f;
+            const float sign = __builtin_bit_cast(float, 0x3f800000u ^ turn ^ (uint32_t)(lane & 16) << 27);
+            e.a1 = ok ? sign * (F * geo.x) : 0.f;
+            e.a2 = ok ? sign * (F * geo.y) : 0.f;
             const int x1 = wave_exponent(e.a1), x2 = wave_exponent(e.a2);
-            e.a1 = ldexpf(e.a1, -x1);
-            e.a2 = ldexpf(e.a2, -x2);
-            up[0] = ldexpf(turn, x1);
-            up[1] = ldexpf(turn, x2);
-            turn = -turn;
+            e.a1 = ldexpf(e.a1, kColumnBits - x1);
+            e.a2 = ldexpf(e.a2, kColumnBits - x2);
+            up[0] = power_bits(x1 - kColumnBits) | turn;
+            up[1] = power_bits(x2 - kColumnBits) | turn;
+            turn ^= 0x80000000u;
             for (int k = 0; k < head; ++k) {
                 const float g0 = gload(reinterpret_cast<const float*>(j.gtab), 2 * (int64_t)k);
                 const float g1 = gload(reinterpret_cast<const float*>(j.gtab), 2 * (int64_t)k + 1);
@@ -227,7 +245,7 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
 #pragma unroll
                 for (int pol = 0; pol < 2; ++pol) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[g][pol][i] = fmaf(sum[pol][i], up[pol], acc[g][pol][i]);
+                    for (int i = 0; i < 16; ++i) acc[g][pol][i] = fmaf(sum[pol][i], __builtin_bit_cast(float, up[pol]), acc[g][pol][i]);
                 }
             };
 #pragma unroll
@@ -255,6 +273,8 @@ __global__ void __launch_bounds__(kMxThreads, mx_waves(RG)) k_accumulate_mx(MxAr
                 }
             }
             add(RG - 1);
+            up[0] ^= 0x80000000u;                          // the next 16 columns' sign
+            up[1] ^= 0x80000000u;
         }
     }
 

@@ -784,7 +784,7 @@ hipError_t fold_part(const rad_grid* g, const AccArgs& a, const GridPart& part, 
                      hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
 {
     return rad::launch_fold(a.part, g->d_S + (int64_t)part.k0 * g->n_dir * 4, a.splits, (int64_t)part.n * g->n_dir * 4,
-                            st, e0, e1);
+                            part.matrix ? rad::kMxScale : 1.0, (int64_t)part.head * g->n_dir, st, e0, e1);
 }
 
 // The job of one part: the general kernel sees the frequencies below the part's end.
