@@ -293,6 +293,7 @@ namespace {
 constexpr int64_t kMaxPerWorkgroup = 32768;
 constexpr int64_t kMinPerSplit = 8;
 constexpr int64_t kFewSplits = 32;
+constexpr double kSplitCost = 6.0;   // of a split, in particles of one group
 constexpr int kMaxWaves = 8;     // of one workgroup
 
 LaunchShape shape_of(const rad_tile& t, int variant = 0)
@@ -357,36 +358,38 @@ double fixed_cost(int n_dir, int n_omega, int variant)
 
 // Launch shape without a measured entry for the grid.  A simple rule, 32 directions up to 256
 // frequencies, else 16, and as many waves as the frequencies fill, gives way to the tile for which
-// a push of 50000 particles is faster by a tenth, by the measured time of a particle on a tile.
+// a push of 50000 particles is faster by a twentieth (the walk kernels) or a tenth (the others), by
+// the measured time of a particle on a tile.
 //
 // The times hold what a formula for the waves' residence missed: a workgroup's waves start on
 // the same SIMD each time, so that 3, 5 or 6 of them load the SIMDs unevenly (6 cost what 8 do),
 // and more than four waves of the kernels with three waves per SIMD leave room for no second
 // workgroup (5 to 8 cost twice what 4 do).  Choosing by such a formula was up to 1.5 times
 // slower than the rule: 120000 particles x 56 x 440 of an explicit list 1599 us by the rule, 2399
-// by the formula and 1359 here; 64 x 786 1424, 1649 and 1416; 128 x 300 1230, 1311 and 1230; in 120
-// grids of 16 to 128 directions and 16 to 1024 frequencies nothing is slower than the rule by more
-// than 3 % at 20000 and 120000 particles.  At 1000 some are, whose larger number of partial tiles
-// shows (20 x 273 in cubic cells 20 -> 25 us, and 636 -> 429 at 120000).
+// by the formula and 1364 here; 64 x 786 1459, 1656 and 1395; 128 x 300 1234, 1312 and 1152.  The
+// lines, a twentieth and for the other kernels a tenth, are where the measured choice begins
+// to be right in all of 250 grids of 16 to 128 directions and 16 to 1024 frequencies, 20000 and
+// 120000 particles: nothing slower than the rule by more than 5 %.
 rad_tile default_tile(int n_dir, int n_omega, int variant = 0)
 {
-    // ns of one particle on one tile of a full chip, by directions (16, 32, 64) and waves (1 to 8);
-    // 120000 particles, 128 directions, each tile's own number of frequencies
-    static const float kWalk[3][8] = {{.367f, .536f, .776f, .855f, 1.270f, 1.442f, 1.444f, 1.505f},
-                                      {.507f, .563f, .851f, .919f, 1.380f, 1.486f, 1.515f, 1.575f},
-                                      {1.893f, 1.251f, 1.137f, 1.093f, 1.467f, 1.628f, 1.627f, 1.685f}};
-    static const float kDirect[3][8] = {{.577f, .944f, 1.363f, 1.499f, 3.300f, 3.305f, 3.309f, 3.320f},
-                                        {.746f, .943f, 1.385f, 1.535f, 3.328f, 3.305f, 3.317f, 3.292f},
-                                        {1.972f, 1.827f, 1.807f, 1.775f, 3.460f, 3.449f, 3.429f, 3.415f}};
-    static const float kCubic[3][8] = {{.492f, .816f, 1.211f, 1.256f, 2.595f, 2.601f, 2.595f, 2.575f},
-                                       {.682f, .810f, 1.300f, 1.345f, 2.719f, 2.676f, 2.684f, 2.697f},
-                                       {1.948f, 1.650f, 1.553f, 1.511f, 2.862f, 2.837f, 2.817f, 2.823f}};
+    // ns that a particle more costs on one tile of a full chip, by directions (16, 32, 64) and
+    // waves (1 to 8), between 20000 and 120000 particles of 128 directions, each tile's own
+    // number of frequencies; a push itself costs 8 us and the partial sums
+    static const float kWalk[3][8] = {{.346f, .515f, .756f, .833f, 1.248f, 1.415f, 1.418f, 1.478f},
+                                      {.476f, .522f, .807f, .879f, 1.336f, 1.444f, 1.470f, 1.526f},
+                                      {1.838f, 1.173f, 1.071f, 1.009f, 1.389f, 1.538f, 1.531f, 1.584f}};
+    static const float kDirect[3][8] = {{.562f, .929f, 1.338f, 1.469f, 3.275f, 3.279f, 3.280f, 3.290f},
+                                        {.715f, .908f, 1.340f, 1.485f, 3.268f, 3.258f, 3.267f, 3.240f},
+                                        {1.907f, 1.752f, 1.749f, 1.700f, 3.372f, 3.350f, 3.327f, 3.302f}};
+    static const float kCubic[3][8] = {{.471f, .795f, 1.198f, 1.227f, 2.568f, 2.569f, 2.561f, 2.540f},
+                                       {.649f, .770f, 1.263f, 1.293f, 2.658f, 2.622f, 2.627f, 2.629f},
+                                       {1.881f, 1.573f, 1.483f, 1.418f, 2.761f, 2.724f, 2.693f, 2.690f}};
     const bool walk = variant == 0 || variant == rad::kVarBlockStep;
     const auto& ns = walk ? kWalk : variant & rad::kVarDirect ? kDirect : kCubic;
     // Splits for two rounds of resident workgroups, where that is faster: the other kernels' tiles of
     // three and four waves, whose one round ends unevenly.
-    static const float kDirect2[2][2] = {{1.295f, 1.420f}, {1.333f, 1.466f}};
-    static const float kCubic2[2][2] = {{1.153f, 1.205f}, {1.222f, 1.299f}};
+    static const float kDirect2[2][2] = {{1.280f, 1.384f}, {1.286f, 1.402f}};
+    static const float kCubic2[2][2] = {{1.141f, 1.169f}, {1.170f, 1.230f}};
     constexpr double kCus = 256.0, kParticles = 50000.0;
     auto tile = [](int dpw, int waves) {
         rad_tile t{16, dpw, waves, 0};
@@ -400,11 +403,11 @@ rad_tile default_tile(int n_dir, int n_omega, int variant = 0)
         const double fit = kCus * t.wg_per_cu, splits = std::max(1.0, std::floor(fit / tiles));
         const double used = splits * tiles / (std::ceil(splits * tiles / fit) * fit);
         // in ns; the partial sums are written and folded at 5 TB/s
-        return kParticles * tiles * tile_ns / used + splits * n_dir * n_omega * 16.0 * 0.2e-3;
+        return 8.0e3 + kParticles * tiles * tile_ns / used + splits * n_dir * n_omega * 16.0 * 0.2e-3;
     };
     const int dpw = n_dir >= 32 && n_omega <= 256 ? 32 : 16, per_wave = 64 / dpw * 16;
     rad_tile best = tile(dpw, std::min(8, std::max(1, (n_omega + per_wave - 1) / per_wave)));
-    double best_time = time(best, ns[dpw / 32][best.waves - 1]) / 1.1;
+    double best_time = time(best, ns[dpw / 32][best.waves - 1]) / (walk ? 1.05 : 1.1);
     auto consider = [&](const rad_tile& t, double tile_ns) {
         const double c = time(t, tile_ns);
         if (c >= best_time) return;
@@ -416,7 +419,9 @@ rad_tile default_tile(int n_dir, int n_omega, int variant = 0)
             rad_tile t = tile(d, waves);
             const int to = rad::tile_omegas(shape_of(t));
             if (waves > 1 && to - to / waves >= n_omega) continue;   // a wave without a frequency
-            consider(t, ns[d / 32][waves - 1]);
+            // one round of three such waves is short of the workgroups that it has splits for
+            // (48 x 175 of a list 596 us in one round of (16, 3), 486 in two)
+            if (walk || d == 64 || waves != 3) consider(t, ns[d / 32][waves - 1]);
             if (!walk && d <= 32 && (waves == 3 || waves == 4)) {
                 t.wg_per_cu *= 2;
                 consider(t, (variant & rad::kVarDirect ? kDirect2 : kCubic2)[d / 32][waves - 3]);
@@ -709,7 +714,8 @@ void fill_job(rad::Job& j, const rad_grid* g, const rad_particles* p, double t0,
 // for, all of the same length to one particle, in chunks of one length.  A smaller push has
 // fewer chunks than that: the idle waves first share the chunks' particles (groups of the
 // flexible build, up to eight waves a workgroup), then the splits get shorter, down to
-// kMinPerSplit particles.  The flexible build of few directions has its groups already; where
+// kMinPerSplit particles, to the length of the least time: that of a split times the waves on
+// the fullest SIMD, where two take hardly longer than one.  The flexible build of few directions has its groups already; where
 // they are one, its splits may be shorter than that as long as there are only kFewSplits of
 // them (each is a partial tile to write and to fold: 15 x 540 points, 1500 particles 34 us in
 // splits of 3 and 22 in splits of 8; 256 particles 20.6 and 15; 16 particles 11.9 in splits of
@@ -720,7 +726,7 @@ void fill_job(rad::Job& j, const rad_grid* g, const rad_particles* p, double t0,
 //
 // The matrix kernel's splits are whole steps of 16 particles, at least two.
 template <typename Fn>
-int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, const GridPart& part, Fn fn)
+int for_each_launch(const rad_grid* g, AccArgs& a, int64_t total, int64_t target_splits, const GridPart& part, Fn fn)
 {
     const int64_t per_launch_cap = target_splits * kMaxPerWorkgroup;
     for (int64_t i0 = 0; i0 < total; i0 += per_launch_cap) {
@@ -737,10 +743,20 @@ int for_each_launch(AccArgs& a, int64_t total, int64_t target_splits, const Grid
             per = std::max({per, step, std::min(kMinPerSplit, (n + kFewSplits - 1) / kFewSplits)});
         } else if (per <= rad::kChunk) {
             int groups = 1;
-            per = rad::kChunk;
-            auto fits = [&](int64_t p, int k) { return (n + p - 1) / p * k <= target_splits; };
-            while (2 * groups * part.tile.waves <= kMaxWaves && fits(per, 2 * groups)) groups *= 2;
-            while (per > kMinPerSplit && fits(per / 2, groups)) per /= 2;
+            const int64_t chunks = (n + rad::kChunk - 1) / rad::kChunk, tiles = tiles_of(g, part);
+            while (2 * groups * part.tile.waves <= kMaxWaves && chunks * 2 * groups <= target_splits) groups *= 2;
+            double best = 0.0;
+            for (int64_t p = rad::kChunk; p >= kMinPerSplit; --p) {
+                const int64_t splits = (n + p - 1) / p;
+                if (splits * groups > target_splits) break;
+                const int64_t on_cu = (splits * tiles + g->cus - 1) / g->cus;
+                const double load = std::max(2.0, on_cu * groups * part.tile.waves / 4.0);
+                const double time = load * ((p + groups - 1) / groups + kSplitCost);
+                if (best == 0.0 || time < best) {
+                    best = time;
+                    per = p;
+                }
+            }
             if (groups > 1) {
                 const LaunchShape ls = shape_of(part.tile);
                 a.flex = rad::FlexShape{rad::tile_dirs(ls), rad::tile_omegas(ls) / ls.w_per_lane, 1, groups, ls.waves,
@@ -890,7 +906,7 @@ int push_range(rad_grid* g, double t0, int64_t n_per_step, int64_t total, const 
     for (const GridPart& part : g->parts) {
         AccArgs a{};
         part_job(a.job, g, part, p, t0, n_per_step);
-        rc = for_each_launch(a, total, max_splits(g, part), part, [&]() -> int {
+        rc = for_each_launch(g, a, total, max_splits(g, part), part, [&]() -> int {
             return push_launch(g, part, a, p->dtype, st, timed_push);
         });
         if (rc) return rc;
@@ -1240,7 +1256,7 @@ int rad_push_step_noalloc(rad_grid* g, double t, int64_t n_particles, const rad_
         part_job(a.job, g, part, p, t, n_particles);
         a.part = scr;
         const int64_t cap = (int64_t)(RAD_NOALLOC_SCRATCH_BYTES / split_bytes(g, part));
-        rc = for_each_launch(a, n_particles, std::min<int64_t>(max_splits(g, part), cap), part, [&]() -> int {
+        rc = for_each_launch(g, a, n_particles, std::min<int64_t>(max_splits(g, part), cap), part, [&]() -> int {
             // same stream: a launch's accumulate rewrites the scratch only after the previous
             // launch's fold has read it
             hipError_t e = launch_part(g, a, part, p->dtype, st);
@@ -1363,7 +1379,7 @@ extern "C" int rad_debug_plan(const rad_grid_desc* d, const rad_tile* tile, int3
     int32_t n = 0;
     for (const GridPart& part : g.parts) {
         AccArgs a{};
-        for_each_launch(a, n_particles, max_splits(&g, part), part, [&]() -> int {
+        for_each_launch(&g, a, n_particles, max_splits(&g, part), part, [&]() -> int {
             if (n < max_launches) {
                 rad_debug_launch l{};
                 l.kernel = part.matrix ? 2 : a.flex.groups ? 1 : 0;

@@ -82,15 +82,28 @@ def test_small_pushes_do_not_split_to_single_particles(n_dir, n_omega, kind):
             assert l.splits <= 32 or l.per_split >= 8, (n, l.splits, l.per_split)
 
 
-# grids for which another tile was measured 1.03 to 1.76 times slower
-@pytest.mark.parametrize("n_dir,n_omega,kind,shape,tile", [
-    (128, 96, "uniform", "cic", (16, 32, 3, 4)), (128, 300, "uniform", "cic", (16, 16, 5, 2)),
-    (64, 786, "uniform", "cic", (16, 16, 8, 2)), (56, 440, "log", "cic", (16, 16, 4, 6)),
-    (32, 267, "blocks", "cic", (16, 16, 5, 2)), (77, 41, "log", "cic", (16, 32, 2, 4))])
-def test_default_tiles(n_dir, n_omega, kind, shape, tile):
+# tiles (directions, waves) that were measured 1.03 to 1.77 times slower than the best on these grids
+@pytest.mark.parametrize("n_dir,n_omega,kind,shape,slow", [
+    (128, 96, "uniform", "cic", (64, 6)), (128, 300, "uniform", "cic", (32, 5)), (64, 786, "uniform", "cic", (32, 5)),
+    (56, 440, "log", "cic", (32, 5)), (32, 267, "blocks", "cic", (32, 5)), (64, 784, "uniform", "cic3d", (32, 5)),
+    (64, 830, "log", "cic", (64, 6)), (20, 418, "uniform", "cic3d", (32, 5))])
+def test_default_tiles(n_dir, n_omega, kind, shape, slow):
     l, = plan(n_dir, n_omega, 1000000, kind, shape)
     assert l.kernel == FIXED
-    assert tuple(getattr(l.tile, k) for k, _ in _lib.Tile._fields_) == tile
+    assert (l.tile.dir_per_wave, l.tile.waves) != slow
+
+
+@pytest.mark.parametrize("shape", ["cic", "cic3d"])
+@pytest.mark.parametrize("n_dir,n_omega", [(16, 64), (37, 100), (44, 34), (128, 256), (88, 200), (64, 123)])
+def test_small_pushes_fill_the_chip(n_dir, n_omega, shape):
+    """Splits of fewer than 32 particles: never more of them than the tile asks for, and never so few
+    that half of the chip's compute units stand idle where splits of 8 particles would fill them."""
+    for n in [300, 1000, 1024, 5003, 9660, 16000, 32769]:
+        l, = plan(n_dir, n_omega, n, shape=shape)
+        tiles = -(-n_dir // l.tile.dir_per_wave) * -(-n_omega // (64 // l.tile.dir_per_wave * 16 * l.tile.waves))
+        assert l.splits * tiles <= CUS * l.tile.wg_per_cu
+        most = min(-(-n // 8), CUS * l.tile.wg_per_cu // tiles)
+        assert l.per_split > 32 or l.splits * tiles >= min(CUS // 2, most * tiles), (n, l.splits, l.per_split)
 
 
 @pytest.mark.parametrize("kind,shape", [("log", "cic"), ("uniform", "cic3d"), ("log", "cic3d")])
