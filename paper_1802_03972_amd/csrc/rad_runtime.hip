@@ -759,10 +759,10 @@ int for_each_launch(const rad_grid* g, AccArgs& a, int64_t total, int64_t target
             const int64_t chunks = (n + rad::kChunk - 1) / rad::kChunk, tiles = tiles_of(g, part);
             while (2 * groups * part.tile.waves <= kMaxWaves && chunks * 2 * groups <= target_splits) groups *= 2;
             double best = 0.0;
-            for (int64_t p = rad::kChunk; p >= kMinPerSplit; --p) {
-                const int64_t splits = (n + p - 1) / p;
+            for (int p = rad::kChunk; p >= kMinPerSplit; p -= 2) {       // in 32 bits: divisions of 64 cost 0.4 us here
+                const int splits = ((int)n + p - 1) / p;
                 if (splits * groups > target_splits) break;
-                const int64_t on_cu = (splits * tiles + g->cus - 1) / g->cus;
+                const int on_cu = (splits * (int)tiles + g->cus - 1) / g->cus;
                 const double load = std::max(2.0, on_cu * groups * part.tile.waves / 4.0);
                 const double time = load * ((p + groups - 1) / groups + kSplitCost);
                 if (best == 0.0 || time < best) {
