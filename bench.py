@@ -23,6 +23,7 @@ import json
 import os
 import sys
 import time
+from functools import partial
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
@@ -30,6 +31,9 @@ if ROOT not in sys.path:
 
 FLOPS_PER_UPDATE = 20          # complex rotate 6 + form-factor scale 2 + 3 complex FMAs 12
 FP32_PEAK_TFLOPS = 157.3       # MI355X FP32 vector peak (published)
+F16_PEAK_TFLOPS = 2516.6       # dense f16 matrix peak: 256 CUs x 4096 flops a cycle x 2.4 GHz
+VALU_PEAK_GINSTR = 1228.8      # 1024 SIMDs, a wave instruction each two cycles at 2.4 GHz
+MATRIX_FLOPS_PER_UPDATE = 48   # of the matrix-core kernel
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E bandwidth (published)
 METRIC = "particle*direction*frequency updates/s (vs FP32 peak); p50/p99 step latency"
 WORKLOADS = ["single_bunch_fp32", "tiny_fp64", "batched_uneven", "serving", "precision_stress",
@@ -106,7 +110,8 @@ def profile_values(profile: str, tile, files=None, suffix: str = "") -> dict:
     except OSError:
         return {}
     vals = {}
-    keys = ("traffic_bytes_per_launch", "executed_fp32_flops_per_update", "tile")
+    keys = ("traffic_bytes_per_launch", "executed_fp32_flops_per_update", "valu_instructions_per_update",
+            "mfma_instructions_per_update", "tile")
     for line in text.splitlines():
         if ":" not in line:
             continue
@@ -119,7 +124,7 @@ def profile_values(profile: str, tile, files=None, suffix: str = "") -> dict:
               if isinstance(tile, dict) else str(tile))
     if vals.get("kernel_source_sha256") != sha or vals.get("tile") != tile_s:
         return {}
-    return {k: float(vals[k]) for k in keys[:2] if k in vals}
+    return {k: float(vals[k]) for k in keys[:-1] if k in vals}
 
 
 def alu_roofline(updates_per_launch: float, avg_ms: float, kernel: str, profile: str = "", tile=None,
@@ -139,6 +144,31 @@ def alu_roofline(updates_per_launch: float, avg_ms: float, kernel: str, profile:
            "frac_executed": None if exe is None else round(achieved / FLOPS_PER_UPDATE * exe / FP32_PEAK_TFLOPS, 4),
            "executed_fp32_flops_per_update": exe,
            "counters_source": f"profiles/{profile}" if pv else None}
+    out.update(extra)
+    return out
+
+
+MATRIX_PROFILE = "k_accumulate_mx_precision_stress.md"
+MATRIX_TILE = "four row groups of 256 frequencies per wave"
+
+
+def matrix_roofline(updates_per_launch: float, avg_ms: float, **extra) -> dict:
+    """Roofline entry of the matrix-core accumulate kernel, which has two bounds: the matrix
+    cores (48 f16 flops per update: 8 multiply-adds of three products of half factors) and, from
+    the profile while its kernel hash matches, the vector ALUs that form the factors (wave
+    instructions, of which a SIMD starts one in two cycles at most)."""
+    from paper_1802_03972_amd.build import MATRIX_FILES
+    rate = updates_per_launch / (avg_ms * 1e-3)
+    achieved = rate * MATRIX_FLOPS_PER_UPDATE / 1e12
+    pv = profile_values(MATRIX_PROFILE, MATRIX_TILE, MATRIX_FILES)
+    per = pv.get("valu_instructions_per_update")
+    valu = None if per is None else {"bound": "valu issue", "achieved": round(rate * per / 64 / 1e9, 1),
+                                     "peak": VALU_PEAK_GINSTR, "unit": "G wave instructions/s",
+                                     "frac": round(rate * per / 64 / 1e9 / VALU_PEAK_GINSTR, 4),
+                                     "instructions_per_update": per, "counters_source": f"profiles/{MATRIX_PROFILE}"}
+    out = {"bound": "matrix", "achieved": round(achieved, 3), "peak": F16_PEAK_TFLOPS, "unit": "TFLOP/s",
+           "frac": round(achieved / F16_PEAK_TFLOPS, 4), "kernel": "k_accumulate_mx", "avg_launch_ms": round(avg_ms, 4),
+           "updates_per_launch": int(updates_per_launch), "flops_per_update": MATRIX_FLOPS_PER_UPDATE, "valu": valu}
     out.update(extra)
     return out
 
@@ -754,13 +784,13 @@ def bench_precision(args) -> dict:
     for name, g in grids.items():
         prof = g.profile_read()
         avg_ms = prof["accumulate_ms"] / max(1, prof["launches"])
+        entry = matrix_roofline if name == "fp64_phase" else partial(alu_roofline, kernel="k_accumulate")
         out_modes[name] = {"updates_per_s_kernel": prof["updates"] / (prof["accumulate_ms"] * 1e-3),
                            "accumulate_ms": prof["accumulate_ms"], "launches": int(prof["launches"]),
                            # a Gaussian far past its underflow: the FP64-phase grid's terms run on the
-                           # matrix cores, against which the FP32 vector peak is no bound
-                           "roofline": alu_roofline(prof["updates"] / max(1, prof["launches"]), avg_ms,
-                                                    "k_accumulate_mx" if name == "fp64_phase" else "k_accumulate",
-                                                    fold_ms_per_launch=round(prof["fold_ms"] / max(1, prof["launches"]), 4))}
+                           # matrix cores
+                           "roofline": entry(prof["updates"] / max(1, prof["launches"]), avg_ms,
+                                             fold_ms_per_launch=round(prof["fold_ms"] / max(1, prof["launches"]), 4))}
     cpu = None
     if use_oracle:
         Iref = oracle.prefactor(w.dt) * np.sum(np.abs(S_ref) ** 2, axis=-1)

@@ -25,6 +25,8 @@ HIPCC_FLAGS = [
 ]
 
 
+# the files that define the matrix-core accumulate kernel
+MATRIX_FILES = ["rad_internal.h", "rad_device.h", "rad_matrix.hip"]
 # the files that define the auxiliary kernels (fold, read-out, tracked particles)
 AUX_FILES = ["rad_internal.h", "rad_device.h", "rad_kernels.hip"]
 
