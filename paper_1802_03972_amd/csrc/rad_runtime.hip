@@ -138,6 +138,14 @@ constexpr size_t kStageHeader = 256;      // the flag's place before the result
 constexpr size_t kMaxStageBytes = (size_t)8 << 20;
 constexpr size_t kStagesKept = 8;
 
+// Allocating and freeing is no work on a stream, but would end a capture that another thread is in
+// the middle of (of the default, global mode).
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 class StagePool {
 public:
     struct Stage {
@@ -158,6 +166,7 @@ public:
             std::lock_guard<std::mutex> lk(mu_);
             if (--users_ == 0) gone.swap(free_);
         }
+        RelaxedCapture relaxed;
         for (const Stage& s : gone) (void)hipHostFree(s.host);
     }
     hipError_t take(size_t bytes, Stage* out)
@@ -176,6 +185,7 @@ public:
         Stage s;
         s.bytes = 64 * 1024;
         while (s.bytes < bytes) s.bytes *= 2;
+        RelaxedCapture relaxed;
         hipError_t e = hipHostMalloc((void**)&s.host, s.bytes, hipHostMallocPortable | hipHostMallocMapped);
         if (e != hipSuccess) return e;
         e = hipHostGetDevicePointer((void**)&s.dev, s.host, 0);
@@ -195,6 +205,7 @@ public:
                 return;
             }
         }
+        RelaxedCapture relaxed;
         (void)hipHostFree(s.host);
     }
 

@@ -69,3 +69,43 @@ def test_calls_refuse_a_capturing_stream(rad):
     g.spectrum_device(out)
     torch.cuda.synchronize()
     assert np.allclose(out.cpu().numpy(), g.spectrum(other))
+
+
+def test_another_thread_reads_during_a_capture(rad):
+    """A host read-out's page-locked buffer may be allocated while another thread captures: that is
+    no work on a stream, and must end neither the read-out nor the capture."""
+    import threading
+    import torch
+    w = SINGLE.scaled(n_particles=300, n_steps=1, nx_dir=4, ny_dir=8, n_omega=2048, seed=77)
+    part = step_slice(to_device(w.steps(), w.in_dtype), 0, w.n_particles)
+    weights = np.ones(w.n_particles)
+    g = rad.Grid(w.directions(), w.omega0, w.domega, w.n_omega, shape=w.shape, shape_len=w.shape_len, dt=w.dt)
+    tr = rad.Tracked(w.directions(), w.omega0, w.domega, w.n_omega, w.n_particles, dt=w.dt)
+    main = torch.cuda.default_stream()
+    g.push_step(0.0, part, main)
+    tr.push_step(0.0, part, main)
+    torch.cuda.synchronize()
+    got = {}
+
+    def read():
+        try:      # several sizes, so that buffers are allocated whatever the pool holds
+            got["I"], got["Z"] = g.spectrum(main), g.spectrum_complex(main)
+            got["tracked"] = tr.spectrum(weights, stream=main)
+        except Exception as e:          # reported below, outside the capture
+            got["error"] = e
+
+    x = torch.zeros(1024, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        x += 1
+        t = threading.Thread(target=read)
+        t.start()
+        t.join()
+        x += 1
+    graph.replay()
+    torch.cuda.synchronize()
+    assert "error" not in got, got["error"]
+    assert float(x[0]) == 2.0
+    assert np.array_equal(got["I"], g.spectrum()) and np.array_equal(got["Z"], g.spectrum_complex())
+    assert np.array_equal(got["tracked"], tr.spectrum(weights))
