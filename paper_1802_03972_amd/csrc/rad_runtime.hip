@@ -767,13 +767,18 @@ int for_each_launch(const rad_grid* g, AccArgs& a, int64_t total, int64_t target
             per = std::max({per, step, std::min(kMinPerSplit, (n + kFewSplits - 1) / kFewSplits)});
         } else if (per <= rad::kChunk) {
             int groups = 1;
-            const int64_t chunks = (n + rad::kChunk - 1) / rad::kChunk, tiles = tiles_of(g, part);
+            const int64_t chunks = (n + rad::kChunk - 1) / rad::kChunk;
             while (2 * groups * part.tile.waves <= kMaxWaves && chunks * 2 * groups <= target_splits) groups *= 2;
+            per = rad::kChunk;
             double best = 0.0;
-            for (int p = rad::kChunk; p >= kMinPerSplit; p -= 2) {       // in 32 bits: divisions of 64 cost 0.4 us here
-                const int splits = ((int)n + p - 1) / p;
-                if (splits * groups > target_splits) break;
-                const int on_cu = (splits * (int)tiles + g->cus - 1) / g->cus;
+            // for each number of workgroups on a CU the shortest splits that make no more (in 32
+            // bits: 64-bit divisions cost a push 0.4 us)
+            const int tiles = tiles_of(g, part), particles = (int)n, target = (int)target_splits;
+            for (int on_cu = 1; on_cu <= part.tile.wg_per_cu; ++on_cu) {
+                const int most = std::min(on_cu * g->cus / tiles, target / groups);
+                if (most < 1) continue;
+                const int p = std::max((int)kMinPerSplit, (particles + most - 1) / most);
+                if (p > rad::kChunk) continue;
                 const double load = std::max(2.0, on_cu * groups * part.tile.waves / 4.0);
                 const double time = load * ((p + groups - 1) / groups + kSplitCost);
                 if (best == 0.0 || time < best) {
