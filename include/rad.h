@@ -271,8 +271,10 @@ int rad_batcher_destroy(rad_batcher* b);
  * equals that of pushing each item on its own, up to FP32 rounding of the partial sums.
  * Requirements: all grids on the batcher's device with the same precision mode, all items
  * of one particle dtype; grid shapes may differ.  The launch shape is the batcher's own
- * (rad_batcher_set_tile), independent of the grids' single-push tiles.  Several items may
- * target the same grid.  Stream-ordered; the host blocks only to recycle a plan buffer
+ * (rad_batcher_set_tile), independent of the grids' single-push tiles.  A batch, and so the
+ * server, has no matrix-core kernel: grids of constant shape factor (rad_set_tile) are faster
+ * pushed one by one where they are large (1e13 terms/s and more against 5e12).  Several items
+ * may target the same grid.  Stream-ordered; the host blocks only to recycle a plan buffer
  * used two calls earlier.  Calls on one batcher must be ordered on one stream. */
 int rad_batcher_push(rad_batcher* b, const rad_batch_item* items, int32_t n_items, void* stream);
 

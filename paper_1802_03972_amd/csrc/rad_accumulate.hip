@@ -239,10 +239,10 @@ __device__ __forceinline__ void accumulate_range(const Job& j, int td, int tw, i
             // the lane's weights for frequencies 4q .. 4q+3
             auto weights = [&](int q, float (&Fv)[4]) {
                 if constexpr (SHAPE3) {
+                    // F^2 = N + (N^2 - N) g(n, omega) (Eq. 12) lies between N and N^2.  Where N^2 is
+                    // the smaller and below 6e-8 N, the rounding of N^2 - N can make it negative: the
+                    // absolute value (an operand modifier, no instruction) keeps the root real.
 #pragma unroll
-                    // F^2 = N + (N^2 - N) g(n, omega) (Eq. 12).  It is at least N^2; the absolute
-                    // value (an operand modifier, no instruction) keeps the rounding of N^2 - N
-                    // from a negative argument where N^2 < 6e-8 N.
                     for (int u = 0; u < 4; ++u)
                         Fv[u] = __builtin_amdgcn_sqrtf(fabsf(fmaf(NN1, gl[4 * q + u], Nm)));
                 } else {
